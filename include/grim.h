@@ -192,9 +192,10 @@ int grim_workspace_size(const grim_index_t *idx, uint64_t n_pairs, const grim_tu
                         uint64_t *bytes);
 
 /* The filter, batched form: one persistent launch over the whole batch.
- * A work-list kernel cuts the pair space into tiles and records the first read
- * of each tile; the filter kernel's wavefronts pull tiles from an atomic
- * counter.  For each pair it writes counts[k] (int32, the accumulation sum, or
+ * The pair space is cut into tiles (of tile_pairs pairs where the caller or
+ * grim_tune chose it, else by the batch's size), a work-list kernel records the
+ * first read of each, and the filter kernel's wavefronts draw tiles from
+ * counters.  For each pair it writes counts[k] (int32, the accumulation sum, or
  * -1 for a bin id >= n_bins or an invalid read) and pass bit k (1 iff
  * counts[k] >= T of the pair's read).  counts (device, n_pairs int32) and
  * pass_bits (device, ceil(n_pairs / 32) words) are written in full.  workspace
@@ -210,7 +211,7 @@ int grim_filter_batch(const grim_index_t *idx, const grim_batch_t *b, int32_t *c
 /* The batched filter for callers that cannot allocate device memory at all:
  * code being captured into a HIP graph, tight serving loops, and harnesses
  * that forbid allocation.  Same computation, outputs and tuning as
- * grim_filter_batch, but no workspace argument: the scratch (tile counter and
+ * grim_filter_batch, but no workspace argument: the scratch (tile counters and
  * the tile -> first read table) lives in a file-scope device array of
  * GRIM_NOALLOC_SCRATCH_BYTES per GPU, which the library holds from its first
  * use on a device until the process ends.  The call allocates nothing (no

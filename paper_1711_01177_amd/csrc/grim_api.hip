@@ -84,16 +84,22 @@ const BatchedVariant *find_variant(uint32_t q, uint32_t g, uint32_t u)
 std::mutex g_tune_mu;
 std::map<std::tuple<int, uint32_t, uint32_t>, grim_tuning_t> g_tune_cache;
 
+// The launch shape a call asks for.  *fixed: its tile was chosen (by the caller
+// or by grim_tune), else it is only the default and the library cuts the pairs
+// by their number.
 int resolve_tuning(const grim_index_t *idx, uint32_t max_len, const grim_tuning_t *tune,
-                   grim_tuning_t *out)
+                   grim_tuning_t *out, bool *fixed)
 {
     grim_tuning_t t;
+    *fixed = tune && tune->tile_pairs;
     grim_default_tuning(idx->q, &t);
     if (!tune) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find({idx->device, idx->q, max_len});
-        if (it != g_tune_cache.end())
+        if (it != g_tune_cache.end()) {
             t = it->second;
+            *fixed = true;
+        }
     } else {
         if (tune->lanes_per_cand)
             t.lanes_per_cand = tune->lanes_per_cand;
@@ -154,6 +160,7 @@ FilterArgs make_args(const grim_index_t *idx, const grim_batch_t *b, int32_t *co
     a.read_len = b->read_len;
     a.read_e = b->read_e;
     a.e_den = b->e_den;
+    a.inv_den = 1.0 / b->e_den;
     a.max_len = b->max_len;
     a.cand_off = b->cand_off;
     a.cand_bin = b->cand_bin;
@@ -162,8 +169,7 @@ FilterArgs make_args(const grim_index_t *idx, const grim_batch_t *b, int32_t *co
     a.counts = counts;
     a.pass_bits = pass_bits;
     a.status = reinterpret_cast<uint32_t *>(ws);
-    a.tile_counter = reinterpret_cast<uint32_t *>(ws) + 1;
-    a.tile_read = reinterpret_cast<const uint32_t *>(reinterpret_cast<char *>(ws) + kWsHeader);
+    a.counters = reinterpret_cast<uint32_t *>(ws) + 1;
     a.npl = planes_for(idx->q, b->max_len);
     return a;
 }
@@ -174,12 +180,74 @@ uint64_t ws_bytes_for(uint64_t n_pairs, uint32_t tile_pairs)
     return (kWsHeader + 4 * n_tiles + 255) & ~255ull;
 }
 
-// Queue the work-list and batched filter kernels on `s`.
-// status (may be null) replaces the workspace's status word as the word the
-// kernels reset and flag.
+// Workgroups of a batched launch that one CU holds at once.  The kernel's waves
+// stay until the tickets are gone and start on tickets of their own, so a grid
+// beyond what is resident leaves work to waves that start last (q = 4, 6.3e6
+// pairs: 298 us at 8 workgroups per CU, 133 us at the 4 that fit).
+hipError_t batched_resident(const BatchedVariant *v, int threads, size_t lds, int *out)
+{
+    static std::mutex mu;
+    static std::map<std::tuple<const void *, int, size_t>, int> cache;
+    std::lock_guard<std::mutex> lk(mu);
+    const auto key = std::make_tuple(v->kernel, threads, lds);
+    auto it = cache.find(key);
+    if (it == cache.end()) {
+        int n = 0;
+        const hipError_t e =
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, v->kernel, threads, lds);
+        if (e != hipSuccess)
+            return e;
+        it = cache.emplace(key, std::max(1, n)).first;
+    }
+    *out = it->second;
+    return hipSuccess;
+}
+
+// How the pairs of a launch are cut into tickets (FilterArgs).
+struct Tickets {
+    uint32_t big_pairs, small_pairs, n_big, n_tickets;
+};
+
+uint64_t div_up(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
+
+// Tickets of a launch that leaves the cut to the library, n_waves waves and
+// room for a table of `room` first reads.  A ticket costs its wave a first round
+// trip (reads, ids, vectors), the planes of one more read and a draw from a
+// counter (2.1e8 a second for the whole GPU), so it holds 512 pairs where each
+// wave gets one of those, and fewer, down to the 64 whose pass bits one wave
+// stores, where waves would idle (q = 5, 4.2e5 pairs: 256 pairs a ticket 48 us,
+// 128 52 us, 64 57 us; 1.1e5 pairs: 64 29 us, 256 35 us, 1024 63 us; q = 4,
+// 6.3e6 pairs: 512 135 us, 256 169 us, bound by the draws).  Vectors of 512
+// bytes and more pay for smaller ones: four tickets a wave at any size, and a
+// tail of 64-pair tickets (one large one's pairs per wave) so that the waves end
+// together.  512-pair tickets are also what the workspace's table is sized for;
+// with the tail it holds 1024-pair ones, and finer cuts than that search.
+Tickets auto_tickets(uint64_t n_pairs, uint64_t n_waves, uint64_t vector_bytes, uint64_t room)
+{
+    const bool wide = vector_bytes >= 512;
+    auto cut = [&](uint32_t big) {
+        Tickets t = {big, wide ? 64u : big, 0, 0};
+        const uint64_t tail = n_waves * big;
+        t.n_big = (uint32_t)(n_pairs > tail ? (n_pairs - tail) / big : 0);
+        t.n_tickets = t.n_big + (uint32_t)div_up(n_pairs - (uint64_t)t.n_big * big, t.small_pairs);
+        return t;
+    };
+    uint32_t big = 512;
+    while (big > 64 && n_pairs * 2 < n_waves * big * (wide ? 8 : 1))
+        big /= 2;
+    const Tickets t = cut(big);
+    if (t.n_tickets <= room || !wide || big < 512)
+        return t;
+    const Tickets t2 = cut(1024);
+    return t2.n_tickets <= room ? t2 : t;
+}
+
+// Queue the work-list and batched filter kernels on `s`.  fixed: the caller
+// chose the tile (every ticket has t.tile_pairs pairs).  status (may be null)
+// replaces the workspace's status word as the word the kernels reset and flag.
 int enqueue_batched(const grim_index_t *idx, const grim_batch_t *b, int32_t *counts,
                     uint32_t *pass_bits, void *ws, uint64_t ws_bytes, const grim_tuning_t &t,
-                    hipStream_t s, uint32_t *status = nullptr)
+                    bool fixed, hipStream_t s, uint32_t *status = nullptr)
 {
     const uint64_t need = ws_bytes_for(b->n_pairs, t.tile_pairs);
     if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 255))
@@ -189,30 +257,38 @@ int enqueue_batched(const grim_index_t *idx, const grim_batch_t *b, int32_t *cou
     FilterArgs a = make_args(idx, b, counts, pass_bits, ws);
     if (status)
         a.status = status;
-    const uint64_t n_tiles = (b->n_pairs + t.tile_pairs - 1) / t.tile_pairs;
-    if (n_tiles >= (1ull << 32) - (1ull << 24))  // the 32-bit tile counter must not wrap
+    const uint64_t n_tiles = div_up(b->n_pairs, t.tile_pairs);
+    if (n_tiles >= (1ull << 32) - (1ull << 24))  // the 32-bit ticket counters must not wrap
         return GRIM_E_UNSUPPORTED;
-    a.n_tiles = (uint32_t)n_tiles;
-    a.tile_pairs = t.tile_pairs;
-    HIP_TRY(launch_worklist(s, b->cand_off, b->n_reads, t.tile_pairs, (uint32_t)n_tiles,
-                            reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(ws) + kWsHeader),
-                            a.status, a.tile_counter));
-    if (n_tiles == 0)
-        return GRIM_OK;
-    const BatchedVariant *v = find_variant(idx->q, t.lanes_per_cand, t.unroll);
-    // planes, then the tile's pass-bit words rounded up to 16-byte units (the
-    // kernel lays each wave's LDS region out the same way)
-    const size_t per_wave =
-        ((size_t)a.npl * vector_words(idx->q) + ((t.tile_pairs / 32 + 3) & ~3u)) * 4;
+    const size_t per_wave = (size_t)a.npl * vector_words(idx->q) * 4;
     int waves = 4;
     while (waves > 1 && per_wave * waves > 65536)
         --waves;
     if (per_wave > 65536)
         return GRIM_E_UNSUPPORTED;
-    uint64_t grid = (uint64_t)cu_count(idx->device) * t.wg_per_cu;
-    const uint64_t useful = (n_tiles + waves - 1) / waves;
+    const BatchedVariant *v = find_variant(idx->q, t.lanes_per_cand, t.unroll);
+    int resident = 0;
+    HIP_TRY(batched_resident(v, 64 * waves, per_wave * waves, &resident));
+    uint64_t grid = (uint64_t)cu_count(idx->device) * std::min<uint32_t>(t.wg_per_cu, resident);
+    const uint64_t room = (ws_bytes - kWsHeader) / 4;
+    Tickets k = {t.tile_pairs, t.tile_pairs, (uint32_t)n_tiles, (uint32_t)n_tiles};
+    if (!fixed)
+        k = auto_tickets(b->n_pairs, grid * waves, idx->vector_bytes, room);
+    a.big_pairs = k.big_pairs;
+    a.small_pairs = k.small_pairs;
+    a.n_big = k.n_big;
+    a.n_tickets = k.n_tickets;
+    // the table of first reads where the workspace holds one; batches cut finer
+    // than it is sized for look the read up themselves
+    a.ticket_read = nullptr;
+    if (k.n_tickets <= room)
+        a.ticket_read = reinterpret_cast<const uint32_t *>(static_cast<char *>(ws) + kWsHeader);
+    const uint64_t useful = div_up(k.n_tickets, waves);
     if (grid > useful)
         grid = useful;
+    HIP_TRY(launch_worklist(s, a, (uint32_t)(grid * waves)));
+    if (k.n_tickets == 0)
+        return GRIM_OK;
     HIP_TRY(launch_filter(v->kernel, dim3((uint32_t)grid), dim3(64 * waves), per_wave * waves, s, a));
     return GRIM_OK;
 }
@@ -484,9 +560,9 @@ extern "C" int grim_default_tuning(uint32_t q, grim_tuning_t *out)
     grim_tuning_t t = {0, 0, 1024, 8};
     switch (q) {
     case 4: t = {2, 8, 1024, 8}; break;
-    case 5: t = {4, 4, 1024, 4}; break;
+    case 5: t = {4, 2, 1024, 4}; break;
     case 6: t = {8, 2, 512, 4}; break;
-    case 7: t = {64, 2, 1024, 8}; break;
+    case 7: t = {32, 2, 1024, 4}; break;
     default: return GRIM_E_UNSUPPORTED;
     }
     *out = t;
@@ -520,7 +596,8 @@ extern "C" int grim_workspace_size(const grim_index_t *idx, uint64_t n_pairs,
     if (!idx || !bytes)
         return GRIM_E_INVALID;
     grim_tuning_t t;
-    int rc = resolve_tuning(idx, kMaxLen, tune, &t);
+    bool fixed = false;
+    int rc = resolve_tuning(idx, kMaxLen, tune, &t, &fixed);
     if (rc)
         return rc;
     // the cached tuning may use a smaller tile: size for the smallest tile
@@ -536,10 +613,11 @@ extern "C" int grim_filter_batch(const grim_index_t *idx, const grim_batch_t *b,
     if (rc)
         return rc;
     grim_tuning_t t;
-    rc = resolve_tuning(idx, b->max_len, tune, &t);
+    bool fixed = false;
+    rc = resolve_tuning(idx, b->max_len, tune, &t, &fixed);
     if (rc)
         return rc;
-    return enqueue_batched(idx, b, counts, pass_bits, workspace, workspace_bytes, t,
+    return enqueue_batched(idx, b, counts, pass_bits, workspace, workspace_bytes, t, fixed,
                            reinterpret_cast<hipStream_t>(stream));
 }
 
@@ -582,7 +660,8 @@ extern "C" int grim_filter_batch_noalloc(const grim_index_t *idx, const grim_bat
     if (!status)
         return GRIM_E_INVALID;
     grim_tuning_t t;
-    rc = resolve_tuning(idx, b->max_len, tune, &t);
+    bool fixed = false;
+    rc = resolve_tuning(idx, b->max_len, tune, &t, &fixed);
     if (rc)
         return rc;
     if (ws_bytes_for(b->n_pairs, t.tile_pairs) > GRIM_NOALLOC_SCRATCH_BYTES)
@@ -592,7 +671,7 @@ extern "C" int grim_filter_batch_noalloc(const grim_index_t *idx, const grim_bat
     if (rc)
         return rc;
     return enqueue_batched(idx, b, counts, pass_bits, ws, GRIM_NOALLOC_SCRATCH_BYTES, t,
-                           reinterpret_cast<hipStream_t>(stream), status);
+                           fixed, reinterpret_cast<hipStream_t>(stream), status);
 }
 
 extern "C" int grim_filter_plain(const grim_index_t *idx, const grim_batch_t *b, int32_t *counts,
@@ -672,14 +751,15 @@ extern "C" int grim_tune(const grim_index_t *idx, const grim_batch_t *sample, in
                 grim_tuning_t t = {(uint32_t)vars[i].g, (uint32_t)vars[i].u, tp, wg};
                 if (workspace_bytes < ws_bytes_for(sample->n_pairs, tp))
                     continue;
-                if (enqueue_batched(idx, sample, counts, pass_bits, workspace, workspace_bytes, t, s))
+                if (enqueue_batched(idx, sample, counts, pass_bits, workspace, workspace_bytes, t,
+                                    true, s))
                     continue;
                 float ms[3];
                 bool fine = true;
                 for (int rep = 0; rep < 3 && fine; ++rep) {
                     fine = hipEventRecord(e0, s) == hipSuccess &&
                            enqueue_batched(idx, sample, counts, pass_bits, workspace,
-                                           workspace_bytes, t, s) == GRIM_OK &&
+                                           workspace_bytes, t, true, s) == GRIM_OK &&
                            hipEventRecord(e1, s) == hipSuccess &&
                            hipEventSynchronize(e1) == hipSuccess &&
                            hipEventElapsedTime(&ms[rep], e0, e1) == hipSuccess;
@@ -992,7 +1072,8 @@ extern "C" int grim_graph_create(const grim_index_t *idx, const grim_batch_t *b,
     if (!out)
         return GRIM_E_INVALID;
     grim_tuning_t t;
-    rc = resolve_tuning(idx, b->max_len, tune, &t);
+    bool fixed = false;
+    rc = resolve_tuning(idx, b->max_len, tune, &t, &fixed);
     if (rc)
         return rc;
     hipStream_t s;
@@ -1003,7 +1084,7 @@ extern "C" int grim_graph_create(const grim_index_t *idx, const grim_batch_t *b,
         (void)hipStreamDestroy(s);
         return hip_fail(e, "hipStreamBeginCapture");
     }
-    rc = enqueue_batched(idx, b, counts, pass_bits, workspace, workspace_bytes, t, s);
+    rc = enqueue_batched(idx, b, counts, pass_bits, workspace, workspace_bytes, t, fixed, s);
     e = hipStreamEndCapture(s, &graph);
     (void)hipStreamDestroy(s);
     if (rc) {

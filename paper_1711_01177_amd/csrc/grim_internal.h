@@ -11,7 +11,13 @@ namespace grim {
 
 constexpr int kWave = 64;
 constexpr uint32_t kMaxLen = GRIM_MAX_READ_LEN;  // longest read the kernels accept
-constexpr uint64_t kWsHeader = 256;      // status word + tile counter, padded
+constexpr uint64_t kWsHeader = 256;      // status word + ticket counters, padded
+// Ticket counters of a batched launch: ticket k is drawn from counter k %
+// kTicketCounters.  One counter hands out 8.8e7 tickets/s (device-scope atomics
+// on one word, 11.4 ns each whatever the number of waves); four of them, 64
+// bytes apart in the header, 2.1e8.
+constexpr uint32_t kTicketCounters = 4;
+constexpr uint32_t kTicketStride = 16;
 
 // Arguments of both filter kernels (passed by value).
 struct FilterArgs {
@@ -23,6 +29,7 @@ struct FilterArgs {
     const uint32_t *read_len;
     const uint32_t *read_e;
     uint32_t e_den;
+    double inv_den;             // 1 / e_den
     uint32_t max_len;
     const uint64_t *cand_off;
     const uint32_t *cand_bin;
@@ -31,10 +38,12 @@ struct FilterArgs {
     int32_t *counts;
     uint32_t *pass_bits;
     uint32_t *status;
-    uint32_t *tile_counter;
-    const uint32_t *tile_read;
-    uint32_t n_tiles;
-    uint32_t tile_pairs;
+    // work of the batched kernel: tickets of consecutive pairs, the first n_big
+    // of big_pairs pairs, the rest of small_pairs (both multiples of 64)
+    uint32_t *counters;         // kTicketCounters words, kTicketStride words apart
+    const uint32_t *ticket_read;  // first read of each ticket, or null: searched
+    uint32_t n_tickets;
+    uint32_t n_big, big_pairs, small_pairs;
     int npl;                    // multiplicity planes reserved per read
 };
 
@@ -98,9 +107,7 @@ hipError_t launch_build(int q, dim3 grid, hipStream_t s, const uint32_t *ref, ui
 hipError_t launch_build_chunked(int q, uint32_t cus, hipStream_t s, const uint32_t *ref,
                                 uint64_t nw, uint64_t G, uint64_t B, uint64_t O, uint64_t n_bins,
                                 uint32_t *out);
-hipError_t launch_worklist(hipStream_t s, const uint64_t *cand_off, uint64_t n_reads,
-                           uint32_t tile_pairs, uint32_t n_tiles, uint32_t *tile_read,
-                           uint32_t *status, uint32_t *counter);
+hipError_t launch_worklist(hipStream_t s, const FilterArgs &a, uint32_t n_waves);
 hipError_t launch_zero(hipStream_t s, uint32_t *p, uint64_t n);
 hipError_t launch_compact(hipStream_t s, const uint32_t *bits, uint64_t n_pairs,
                           const uint64_t *cand_off, uint64_t n_reads, const uint32_t *cand_bin,

@@ -65,18 +65,15 @@ __device__ __forceinline__ uint32_t popc_and(const uint4 &a, const uint4 &b)
     return __popc(a.x & b.x) + __popc(a.y & b.y) + __popc(a.z & b.z) + __popc(a.w & b.w);
 }
 
-// Build the multiplicity bit planes of one read's tokens in LDS (one wave).
-// planes holds npl planes of VW words each.  Returns the number of planes in
-// use (0 for a read without tokens).  npl is chosen by the host so that
+// Add one read's tokens to its multiplicity bit planes in LDS (one wave); the
+// npl planes of VW words each are zero on entry.  Returns the number of planes
+// in use (0 for a read without tokens).  npl is chosen by the host so that
 // 2^npl > ntok, hence no carry can leave the last plane.
 template <int Q>
-__device__ int build_planes(uint32_t *planes, int npl, const uint32_t *__restrict__ rw, uint64_t nw,
-                            uint64_t off, uint32_t ntok, int lane)
+__device__ int add_planes(uint32_t *planes, int npl, const uint32_t *__restrict__ rw, uint64_t nw,
+                          uint64_t off, uint32_t ntok, int lane)
 {
     constexpr int VW = (1 << (2 * Q)) >> 5;
-    for (int i = lane; i < npl * VW; i += kWave)
-        planes[i] = 0u;
-    wave_fence();
     int top = 0;
     for (uint32_t i = lane; i < ntok; i += kWave) {
         const uint32_t t = token_at<Q>(rw, nw, off + i);
@@ -94,6 +91,18 @@ __device__ int build_planes(uint32_t *planes, int npl, const uint32_t *__restric
         top = max(top, __shfl_xor(top, s));
     wave_fence();
     return top;
+}
+
+// The same on planes with any contents: clears them first.
+template <int Q>
+__device__ int build_planes(uint32_t *planes, int npl, const uint32_t *__restrict__ rw, uint64_t nw,
+                            uint64_t off, uint32_t ntok, int lane)
+{
+    constexpr int VW = (1 << (2 * Q)) >> 5;
+    for (int i = lane; i < npl * VW; i += kWave)
+        planes[i] = 0u;
+    wave_fence();
+    return add_planes<Q>(planes, npl, rw, nw, off, ntok, lane);
 }
 
 __device__ __forceinline__ void flag(uint32_t *status, uint32_t f)
@@ -136,22 +145,36 @@ __global__ __launch_bounds__(256) void build_bins_kernel(const uint32_t *__restr
 }
 
 // ---------------------------------------------------------------- work list
-// Thread i < n_tiles records the read that owns pair i * tile_pairs: the last
-// read r with cand_off[r] <= i * tile_pairs.  Thread 0 also resets the status
-// word and the tile counter of this launch.
+// Ticket k of the batched filter is one run of consecutive pairs: the first
+// n_big tickets hold big_pairs pairs each, the rest small_pairs.
+__device__ __forceinline__ uint64_t ticket_start(uint32_t k, uint32_t n_big, uint32_t big_pairs,
+                                                 uint32_t small_pairs)
+{
+    return k < n_big ? (uint64_t)k * big_pairs
+                     : (uint64_t)n_big * big_pairs + (uint64_t)(k - n_big) * small_pairs;
+}
+
+// Thread i < n_table records the read that owns the first pair of ticket i: the
+// last read r with cand_off[r] <= that pair.  Thread 0 also resets the status
+// word and the ticket counters of this launch: wave w of the n_waves that the
+// filter runs starts with ticket w, so counter c starts at the number of waves
+// w with w % kTicketCounters == c.
 __global__ __launch_bounds__(256) void worklist_kernel(const uint64_t *__restrict__ cand_off,
-                                                       uint64_t n_reads, uint32_t tile_pairs,
-                                                       uint32_t n_tiles, uint32_t *tile_read,
-                                                       uint32_t *status, uint32_t *counter)
+                                                       uint64_t n_reads, uint32_t n_table,
+                                                       uint32_t n_big, uint32_t big_pairs,
+                                                       uint32_t small_pairs, uint32_t n_waves,
+                                                       uint32_t *ticket_read, uint32_t *status,
+                                                       uint32_t *counters)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) {
         *status = 0u;
-        *counter = 0u;
+        for (uint32_t c = 0; c < kTicketCounters; ++c)
+            counters[c * kTicketStride] = (n_waves + kTicketCounters - 1 - c) / kTicketCounters;
     }
-    if (i >= n_tiles || n_reads == 0)
+    if (i >= n_table || n_reads == 0)
         return;
-    const uint64_t p = i * tile_pairs;
+    const uint64_t p = ticket_start((uint32_t)i, n_big, big_pairs, small_pairs);
     uint64_t lo = 0, hi = n_reads - 1;
     while (lo < hi) {
         const uint64_t mid = (lo + hi + 1) >> 1;
@@ -160,7 +183,7 @@ __global__ __launch_bounds__(256) void worklist_kernel(const uint64_t *__restric
         else
             hi = mid - 1;
     }
-    tile_read[i] = (uint32_t)lo;
+    ticket_read[i] = (uint32_t)lo;
 }
 
 __global__ void zero_words_kernel(uint32_t *p, uint64_t n)
@@ -171,177 +194,442 @@ __global__ void zero_words_kernel(uint32_t *p, uint64_t n)
 }
 
 // ----------------------------------------------------------- batched filter
-// Persistent kernel.  Each wavefront repeatedly takes the next tile of
-// tile_pairs consecutive pairs (atomic counter), walks the reads that own the
-// tile's pairs, builds each read's planes once, and processes its candidates
-// with NG = 64 / G lane groups, U candidates in flight per group.  Pass bits of
-// the tile accumulate in LDS and are stored as whole words at the end of the
-// tile (tiles start on multiples of 64 pairs, so no other wave writes them).
+// x of lane ^ m (m a power of two known at compile time after unrolling): DPP
+// moves where one exists, the LDS crossbar otherwise.
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int m)
+{
+    switch (m) {
+    case 1: return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);    // quad_perm 1,0,3,2
+    case 2: return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);    // quad_perm 2,3,0,1
+    case 4: return __builtin_amdgcn_ds_swizzle(x, 4 << 10 | 0x1F);
+    case 8: return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);   // row_ror 8
+    case 16: return __builtin_amdgcn_ds_swizzle(x, 16 << 10 | 0x1F);
+    default: return __shfl_xor(x, m);
+    }
+}
+
+// Sums acc[0 .. U) over the G lanes of a group: lane lg ends with the group's
+// total of acc[lg % U] (U <= G).  log2 U exchange steps halve the values that
+// travel, the rest of the group is a butterfly on the one value left.
+template <int G, int U>
+__device__ __forceinline__ uint32_t group_sums(uint32_t (&acc)[U], int lane)
+{
+#pragma unroll
+    for (int n = U / 2, m = 1; n >= 1; n /= 2, m *= 2) {
+        const bool hi = (lane & m) != 0;
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const uint32_t keep = hi ? acc[2 * j + 1] : acc[2 * j];
+            const uint32_t send = hi ? acc[2 * j] : acc[2 * j + 1];
+            acc[j] = keep + lane_xor(send, m);
+        }
+    }
+#pragma unroll
+    for (int m = U; m < G; m *= 2)
+        acc[0] += lane_xor(acc[0], m);
+    return acc[0];
+}
+
+// Bin id of pair u of a group, ids held one pair a lane, the group's first pair
+// in lane `first`: within a quad a DPP broadcast where a group is one.
+template <int G, int U>
+__device__ __forceinline__ uint32_t group_id(uint32_t ids, int first, int u)
+{
+    if constexpr (G == 4 && U == 4) {
+        switch (u) {
+        case 0: return __builtin_amdgcn_mov_dpp(ids, 0x00, 0xF, 0xF, true);
+        case 1: return __builtin_amdgcn_mov_dpp(ids, 0x55, 0xF, 0xF, true);
+        case 2: return __builtin_amdgcn_mov_dpp(ids, 0xAA, 0xF, 0xF, true);
+        default: return __builtin_amdgcn_mov_dpp(ids, 0xFF, 0xF, 0xF, true);
+        }
+    }
+    return __shfl(ids, first + u);
+}
+
+// Read that owns pair p: the last r with cand_off[r] <= p, found by the whole wave 64 ways at a time (one memory round trip per factor
+// of 64 reads).
+__device__ __forceinline__ uint64_t wave_read_of(const uint64_t *__restrict__ cand_off,
+                                                 uint64_t n_reads, uint64_t p, int lane)
+{
+    uint64_t lo = 0, n = n_reads;   // the answer is in [lo, lo + n)
+    while (n > 1) {
+        const uint64_t step = (n + kWave - 1) / kWave;
+        const uint64_t i = lo + (uint64_t)lane * step;
+        const bool le = (uint64_t)lane * step < n && cand_off[i] <= p;
+        const uint64_t m = __ballot(le);
+        // highest lane at or below p (lane 0's read when none is)
+        const int h = m ? 63 - __builtin_clzll(m) : 0;
+        const uint64_t left = n - (uint64_t)h * step;
+        lo += (uint64_t)h * step;
+        n = left < step ? left : step;
+    }
+    return lo;
+}
+
+// Bit planes of one read's tokens (as build_planes), from the wave's registers:
+// lane l holds packed word l from the read's first one on, the read starting at
+// base po of lane 0's word and ending inside lane 63's.  Four tokens per lane
+// are in flight, and a carry level runs only when some lane needs it, so the
+// number of planes in use comes out uniform without a reduction.  The planes
+// are zero on entry.
+template <int Q>
+__device__ __forceinline__ int build_planes_lanes(uint32_t *planes, int npl, uint32_t word,
+                                                  uint32_t po, uint32_t ntok, int lane)
+{
+    constexpr int VW = (1 << (2 * Q)) >> 5;
+    int np = 0;
+    for (uint32_t base = 0; base < ntok; base += 4 * kWave) {
+        uint32_t tok[4], old[4];
+        constexpr uint32_t kIdle = ~0u;   // no token, or its carry has ended
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            tok[t] = kIdle;
+            old[t] = 0u;
+            if (base + t * kWave < ntok) {   // uniform
+                const uint32_t i = base + t * kWave + lane;
+                const uint32_t pos = po + i;
+                const uint32_t sh = (pos & 15u) << 1;
+                const uint32_t h = __shfl(word, (int)(pos >> 4)), l = __shfl(word, (int)(pos >> 4) + 1);
+                if (i < ntok)
+                    tok[t] = (uint32_t)(((((uint64_t)h << 32) | l) << sh) >> (64 - 2 * Q));
+            }
+        }
+        for (int k = 0; k < npl; ++k) {
+            bool any = false;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                any |= tok[t] != kIdle;
+            if (!__ballot(any))
+                break;
+            np = max(np, k + 1);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (tok[t] != kIdle)
+                    old[t] = atomicXor(&planes[k * VW + (tok[t] >> 5)], 1u << (tok[t] & 31u));
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (!((old[t] >> (tok[t] & 31u)) & 1u))
+                    tok[t] = kIdle;
+        }
+    }
+    return np;
+}
+
+// x / d, rounded down, for x < 2^52: the product with the rounded reciprocal is
+// off by less than one either way.  (A 64-bit integer division would need more
+// registers than the rest of the reads' setup.)
+__device__ __forceinline__ uint64_t div_by(uint64_t x, uint32_t d, double inv)
+{
+    uint64_t q = (uint64_t)((double)x * inv);
+    const int64_t r = (int64_t)(x - q * d);
+    if (r < 0)
+        --q;
+    else if (r >= (int64_t)d)
+        ++q;
+    return q;
+}
+
+// Persistent kernel.  A wavefront takes tickets (runs of consecutive pairs; the
+// first one by its own number, later ones from a counter, drawn while the ticket
+// before is worked on) and goes through a ticket's pairs in blocks of 64 and
+// steps of 64 / G x U pairs, G lanes a pair.
+//
+// What bounds it is the gather of bin vectors (random lines of a multi-GB index,
+// or of the caches), so the loads are kept apart from everything else: a step's
+// vectors are requested one step ahead, by bin id alone, whatever reads the pairs
+// belong to, and the ids two blocks ahead.  The metadata of 64 reads at a time
+// sits in the lanes (CSR range, length, offset, threshold), and the next read's
+// packed bases are requested while the current one's candidates are counted, so
+// a short candidate list costs the building of its planes and no round trips.
+// A step that several reads share is counted once per read, each with its own
+// planes.  Group g of a step owns U consecutive pairs, and the lane sums are
+// exchanged so that lane g * G + u ends with pair g * U + u: a block's 64 counts
+// leave in one coalesced store and its pass bits are one ballot (no LDS, no
+// atomics; tickets start on multiples of 64 pairs, so no two waves share a
+// word).
+//
+// Measured, against the kernel before it (one round trip after another per read,
+// every tile of 1024 pairs drawn from one counter at 11.4 ns a draw): 64 reads x
+// 64 pairs 9.7 us (47.6, of which 4.5 the work list), 100k reads / 2.1e7 pairs on
+// a 64 MB index 436 us (521; a gather of as many vectors alone takes 372), 8.3e8
+// pairs on the 2 GB index 20.0 ms (20.5; gather alone 19.9), q = 6, 2.0e8 pairs
+// 16.5 ms (17.2), q = 7, 5.1e6 pairs of reads up to 2000 bases 1.40 ms (2.66).
+//
+// Registers: two steps of vectors and planes 0 and 1, 8 C (U + 1) of them, beside
+// about 80 others; waves per SIMD as many as that leaves room for.
+constexpr int batched_waves(int c, int u)
+{
+    return 8 * c * (u + 1) <= 48 ? 4 : 8 * c * (u + 1) <= 80 ? 3 : 2;
+}
+
 template <int Q, int G, int U>
-__global__ __launch_bounds__(256) void filter_batched_kernel(FilterArgs a)
+__global__ __launch_bounds__(256, batched_waves((1 << (2 * Q)) / 128 / G, U)) void filter_batched_kernel(
+    FilterArgs a)
 {
     constexpr int VW = (1 << (2 * Q)) >> 5;  // 32-bit words per vector
     constexpr int CH = VW / 4;               // 16-byte slices per vector
     constexpr int C = CH / G;                // slices per lane
-    constexpr int NG = kWave / G;            // candidates per wave step
+    constexpr int NG = kWave / G;            // candidates per load
+    constexpr int SZ = NG * U;               // pairs per step
+    constexpr int SPB = kWave / SZ;          // steps per block
     static_assert(C >= 1 && CH % G == 0, "lane group wider than the vector");
+    static_assert(U <= G && (SPB == 1 || SPB % 2 == 0), "a step is at most one block");
+    constexpr int32_t kNone = 0x7fffffff;    // threshold of a pair without a valid read
 
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int npl = a.npl;
-    const uint32_t mask_words = a.tile_pairs >> 5;
-    // each wave's region: its planes, then the tile's pass-bit words rounded up
-    // to whole 16-byte units, so that every region (and plane) starts 16-byte
-    // aligned for the uint4 plane reads
-    uint32_t *planes = lds + (size_t)wv * (npl * VW + ((mask_words + 3u) & ~3u));
-    uint32_t *tmask = planes + npl * VW;
+    uint32_t *planes = lds + (size_t)wv * npl * VW;
+    uint4 *planes4 = reinterpret_cast<uint4 *>(planes);
     const int g = lane / G, lg = lane % G;
+    // lane (within a block) -> the lane of its step that holds its pair's sum
+    const int src_lane = (lane % SZ) / U * G + (lane % SZ) % U;
 
-    for (;;) {
-        uint32_t tile = 0;
+    const uint32_t wave = uniform_u32(blockIdx.x * (blockDim.x >> 6) + wv);
+    const uint32_t shard = wave % kTicketCounters;
+    uint32_t ticket = wave;
+    for (int i = lane; i < npl * (VW / 4); i += kWave)
+        planes4[i] = make_uint4(0, 0, 0, 0);
+    int np = 0;                              // planes in use (the others are zero)
+
+    while (ticket < a.n_tickets) {
+        uint32_t drawn = 0;
         if (lane == 0)
-            tile = atomicAdd(a.tile_counter, 1u);
-        tile = uniform_u32(__shfl(tile, 0));
-        if (tile >= a.n_tiles)
-            break;
-        const uint64_t t0 = (uint64_t)tile * a.tile_pairs;
-        const uint64_t t1 = min(t0 + a.tile_pairs, a.n_pairs);
-        for (uint32_t i = lane; i < mask_words; i += kWave)
-            tmask[i] = 0u;
-        wave_fence();
+            drawn = atomicAdd(a.counters + shard * kTicketStride, 1u);
+        const uint64_t t0 = ticket_start(ticket, a.n_big, a.big_pairs, a.small_pairs);
+        const uint64_t room = a.n_pairs - t0;
+        const uint32_t span = ticket < a.n_big ? a.big_pairs : a.small_pairs;
+        const uint32_t len = room < span ? (uint32_t)room : span;   // pairs of this ticket
+        const uint32_t *ids_at = a.cand_bin + t0;
 
-        uint64_t r = a.tile_read[tile];
-        r = uniform_u64(r);
-        uint64_t p = t0;
-        while (p < t1) {
-            if (r >= a.n_reads) {  // pairs beyond the last read's range
+        // ------------------------------------------------ bin ids and vectors
+        auto load_ids = [&](uint32_t b) -> uint32_t {
+            const uint32_t x = b + lane;
+            return x < len ? ids_at[x] : 0u;
+        };
+        auto gather = [&](uint4 (&v)[U][C], uint32_t ids, int s) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t id = group_id<G, U>(ids, s * SZ + g * U, u);
+                // an id out of range reads vector 0; its count is replaced below
+                const uint4 *src = a.vec + (uint64_t)(id < a.n_bins ? id : 0u) * CH + lg;
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    v[u][c] = src[c * G];
+            }
+        };
+        uint32_t ids_cur = load_ids(0), ids_nxt = load_ids(kWave);
+
+        // ---------------------------------------------- the ticket's reads
+        // lane l holds read r0 + l: its CSR range within the ticket, offset,
+        // tokens and threshold (kNone: the read is invalid)
+        uint64_t r0, m_off = 0;
+        uint32_t m_beg = 0, m_end = 0, m_tok = 0;
+        int32_t m_thr = kNone;
+        auto load_reads = [&]() {
+            const uint64_t r = r0 + lane;
+            m_beg = m_end = m_tok = 0;
+            m_thr = kNone;
+            if (r < a.n_reads) {
+                const uint64_t cb = a.cand_off[r], ce = a.cand_off[r + 1];
+                const uint32_t L = a.read_len[r], e_num = a.read_e[r];
+                m_off = a.read_off[r];
+                const uint64_t nbases = a.nw * 16;
+                m_beg = cb <= t0 ? 0u : (cb - t0 >= len ? len : (uint32_t)(cb - t0));
+                m_end = ce <= t0 ? 0u : (ce - t0 >= len ? len : (uint32_t)(ce - t0));
+                if (!(L > a.max_len || m_off > nbases || L > nbases - m_off)) {
+                    m_tok = L >= (uint32_t)Q ? L - Q + 1 : 0u;
+                    const uint64_t E = div_by((uint64_t)e_num * L + a.e_den - 1, a.e_den, a.inv_den);
+                    const int64_t T = (int64_t)m_tok - (int64_t)Q * (int64_t)E;
+                    m_thr = T > 0 ? (int32_t)T : 0;   // counts are never negative
+                }
+            }
+        };
+        // packed words of the read in lane j from its first one on, one a lane
+        auto load_words = [&](int j) -> uint32_t {
+            const uint64_t w = (((uint64_t)(uint32_t)__shfl((uint32_t)(m_off >> 32), j) << 32 |
+                                 (uint32_t)__shfl((uint32_t)m_off, j)) >> 4) + lane;
+            return w < a.nw ? a.rw[w] : 0u;
+        };
+        uint32_t first_read = a.ticket_read ? a.ticket_read[ticket] : 0u;
+        uint4 v0[U][C], v1[U][C];
+        gather(v0, ids_cur, 0);
+        if (!a.ticket_read)
+            first_read = (uint32_t)wave_read_of(a.cand_off, a.n_reads, t0, lane);
+        r0 = uniform_u32(first_read);
+        load_reads();
+
+        uint32_t seg_end = 0;       // pairs [.., seg_end) belong to the current segment
+        int32_t thr = kNone;        // its threshold; kNone when it has no valid read
+        int j_next = 0;             // first lane not yet looked at
+        int j_words = -1;           // lane whose read's words are in `words`
+        uint32_t words = 0;
+        uint4 p0[C], p1[C];
+
+        // the segment that holds pair pos
+        auto advance = [&](uint32_t pos) {
+            thr = kNone;
+            uint64_t m;
+            for (;;) {
+                m = j_next < kWave ? __ballot(m_end > pos) >> j_next << j_next : 0ull;
+                if (m)
+                    break;
+                r0 += kWave;
+                j_next = 0;
+                j_words = -1;
+                if (r0 >= a.n_reads) {   // pairs beyond the last read's range
+                    if (lane == 0)
+                        flag(a.status, GRIM_FLAG_CAND_OFF);
+                    seg_end = len;
+                    return;
+                }
+                load_reads();
+            }
+            const int j = (int)uniform_u32((uint32_t)__builtin_ctzll(m));
+            const uint32_t beg = __builtin_amdgcn_readlane(m_beg, j);
+            if (beg > pos) {   // a gap owned by no read: cand_off is not a CSR array
                 if (lane == 0)
                     flag(a.status, GRIM_FLAG_CAND_OFF);
-                for (uint64_t k = p + lane; k < t1; k += kWave)
-                    a.counts[k] = -1;
-                break;
+                seg_end = beg;
+                j_next = j;
+                return;
             }
-            const uint64_t cb = uniform_u64(a.cand_off[r]);
-            const uint64_t ce = uniform_u64(a.cand_off[r + 1]);
-            if (ce <= p) {
-                ++r;
-                continue;
-            }
-            if (cb > p) {  // a gap owned by no read: cand_off is not a CSR array
-                const uint64_t ge = min(cb, t1);
-                if (lane == 0)
-                    flag(a.status, GRIM_FLAG_CAND_OFF);
-                for (uint64_t k = p + lane; k < ge; k += kWave)
-                    a.counts[k] = -1;
-                p = ge;
-                continue;
-            }
-            const uint64_t pe = min(ce, t1);
-            const uint32_t L = uniform_u32(a.read_len[r]);
-            const uint64_t off = uniform_u64(a.read_off[r]);
-            const uint64_t nbases = a.nw * 16;
-            if (L > a.max_len || off > nbases || L > nbases - off) {
+            seg_end = __builtin_amdgcn_readlane(m_end, j);
+            j_next = j + 1;
+            thr = (int32_t)__builtin_amdgcn_readlane((uint32_t)m_thr, j);
+            if (thr == kNone) {
                 if (lane == 0)
                     flag(a.status, GRIM_FLAG_READ);
-                for (uint64_t k = p + lane; k < pe; k += kWave)
-                    a.counts[k] = -1;
-                p = pe;
-                ++r;
-                continue;
+                return;
             }
-            const uint32_t ntok = L >= (uint32_t)Q ? L - Q + 1 : 0u;
-            // bin ids of the segment's first step are requested before the
-            // planes are built, and every step requests the next step's ids
-            // before gathering its own vectors
-            constexpr int STEP = NG * U;
-            auto load_ids = [&](uint64_t c) -> uint32_t {
-                if constexpr (STEP <= kWave) {
-                    const uint64_t kk = c + lane;
-                    return (lane < STEP && kk < pe) ? a.cand_bin[kk] : 0u;
-                } else {
-                    return 0u;
-                }
-            };
-            uint32_t next_ids = load_ids(p);
-            const int np = build_planes<Q>(planes, npl, a.rw, a.nw, off, ntok, lane);
-            const uint32_t e_num = uniform_u32(a.read_e[r]);
-            const uint64_t E = ((uint64_t)e_num * L + a.e_den - 1) / a.e_den;
-            const int64_t T = (int64_t)ntok - (int64_t)Q * (int64_t)E;
-
+            const uint32_t ntok = __builtin_amdgcn_readlane(m_tok, j);
+            const uint32_t po = __builtin_amdgcn_readlane((uint32_t)m_off, j) & 15u;
+            wave_fence();
+            for (int i = lane; i < np * (VW / 4); i += kWave)
+                planes4[i] = make_uint4(0, 0, 0, 0);
+            wave_fence();
+            if (po + ntok + Q <= 16u * kWave) {
+                if (j_words != j)
+                    words = load_words(j);
+                np = build_planes_lanes<Q>(planes, npl, words, po, ntok, lane);
+                wave_fence();
+            } else {
+                const uint64_t off =
+                    (uint64_t)__builtin_amdgcn_readlane((uint32_t)(m_off >> 32), j) << 32 |
+                    __builtin_amdgcn_readlane((uint32_t)m_off, j);
+                np = add_planes<Q>(planes, npl, a.rw, a.nw, off, ntok, lane);
+            }
             // planes 0 and 1 stay in registers for the whole segment
-            uint4 p0[C], p1[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const int w = (c * G + lg) * 4;
-                p0[c] = np > 0 ? *reinterpret_cast<const uint4 *>(planes + w) : make_uint4(0, 0, 0, 0);
-                p1[c] = np > 1 ? *reinterpret_cast<const uint4 *>(planes + VW + w)
-                               : make_uint4(0, 0, 0, 0);
+                p0[c] = planes4[c * G + lg];
+                p1[c] = npl > 1 ? planes4[VW / 4 + c * G + lg] : make_uint4(0, 0, 0, 0);
             }
+            // the words of the next read of this ticket
+            const uint64_t after =
+                j_next < kWave && seg_end < len ? __ballot(m_end > seg_end) >> j_next << j_next : 0ull;
+            if (after) {
+                j_words = (int)uniform_u32((uint32_t)__builtin_ctzll(after));
+                words = load_words(j_words);
+            }
+        };
 
-            for (uint64_t c0 = p; c0 < pe; c0 += (uint64_t)STEP) {
-                uint32_t bin[U];
-                bool ok[U], inr[U];
-                if constexpr (STEP <= kWave) {
-                    const uint32_t mine = next_ids;
-                    next_ids = load_ids(c0 + STEP);
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        bin[u] = __shfl(mine, u * NG + g);
-                } else {
+        int32_t res;    // count of pair b + lane, -1 until one is known
+        int32_t my_thr; // and its read's threshold
+        // counts of step s of block b (vectors in v)
+        auto count = [&](const uint4 (&v)[U][C], uint32_t b, int s) {
+            uint32_t pos = b + s * SZ;
+            const uint32_t pe = min(pos + SZ, len);
+            while (pos < pe) {
+                if (pos >= seg_end)
+                    advance(pos);
+                const uint32_t e = min(seg_end, pe);
+                if (thr != kNone) {
+                    uint32_t acc[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const uint64_t kk = c0 + (uint64_t)u * NG + g;
-                        bin[u] = kk < pe ? a.cand_bin[kk] : 0u;
+                        uint32_t a0 = 0, a1 = 0;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            a0 += popc_and(p0[c], v[u][c]);
+                            a1 += popc_and(p1[c], v[u][c]);
+                        }
+                        acc[u] = a0 + (a1 << 1);
                     }
-                }
-                uint4 v[U][C];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint64_t kk = c0 + (uint64_t)u * NG + g;
-                    ok[u] = kk < pe;
-                    inr[u] = ok[u] && bin[u] < a.n_bins;
-                    const uint4 *src = a.vec + (uint64_t)bin[u] * CH + lg;
-#pragma unroll
-                    for (int c = 0; c < C; ++c)
-                        v[u][c] = inr[u] ? src[c * G] : make_uint4(0, 0, 0, 0);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    uint32_t acc = 0;
-#pragma unroll
-                    for (int c = 0; c < C; ++c)
-                        acc += popc_and(p0[c], v[u][c]) + (popc_and(p1[c], v[u][c]) << 1);
                     for (int k = 2; k < np; ++k) {
 #pragma unroll
                         for (int c = 0; c < C; ++c) {
-                            const uint4 pk = *reinterpret_cast<const uint4 *>(
-                                planes + k * VW + (c * G + lg) * 4);
-                            acc += popc_and(pk, v[u][c]) << k;
+                            const uint4 pk = planes4[k * (VW / 4) + c * G + lg];
+#pragma unroll
+                            for (int u = 0; u < U; ++u)
+                                acc[u] += popc_and(pk, v[u][c]) << k;
                         }
                     }
-#pragma unroll
-                    for (int s = G / 2; s >= 1; s >>= 1)
-                        acc += __shfl_xor(acc, s);
-                    if (lg == 0 && ok[u]) {
-                        const uint64_t kk = c0 + (uint64_t)u * NG + g;
-                        const int32_t cnt = inr[u] ? (int32_t)acc : -1;
-                        a.counts[kk] = cnt;
-                        if (!inr[u])
-                            flag(a.status, GRIM_FLAG_BIN_RANGE);
-                        else if ((int64_t)cnt >= T)
-                            atomicOr(&tmask[(kk - t0) >> 5], 1u << ((kk - t0) & 31u));
+                    uint32_t sum = group_sums<G, U>(acc, lane);
+                    if constexpr (!(SPB == 1 && U == G))
+                        sum = __shfl(sum, src_lane);
+                    const uint32_t x = b + lane;
+                    if (x >= pos && x < e) {
+                        res = (int32_t)sum;
+                        my_thr = thr;
                     }
                 }
+                pos = e;
             }
-            wave_fence();  // planes are rebuilt by the next segment
-            p = pe;
-            ++r;
+        };
+        auto finish = [&](uint32_t b) {
+            const uint32_t x = b + lane;
+            if (my_thr != kNone && ids_cur >= a.n_bins) {   // lanes past len hold id 0
+                res = -1;
+                flag(a.status, GRIM_FLAG_BIN_RANGE);
+            }
+            if (x < len)
+                a.counts[t0 + x] = res;
+            const uint64_t bits = __ballot(res >= my_thr);
+            const uint32_t n_words = (min(len - b, (uint32_t)kWave) + 31) >> 5;
+            if ((uint32_t)lane < n_words)
+                a.pass_bits[((t0 + b) >> 5) + lane] = (uint32_t)(lane ? bits >> 32 : bits);
+        };
+        // one block: x0 holds its first step's vectors; leaves the next block's
+        // first step in x0 (several steps a block) or x1 (one)
+        auto block = [&](uint32_t b, uint4 (&x0)[U][C], uint4 (&x1)[U][C]) {
+            const uint32_t ids_new = load_ids(b + 2 * kWave);
+            res = -1;
+            my_thr = kNone;
+            if constexpr (SPB == 1) {
+                if (b + kWave < len)
+                    gather(x1, ids_nxt, 0);
+                count(x0, b, 0);
+            } else {
+#pragma unroll 1
+                for (int s = 0; s < SPB; s += 2) {
+                    if (b + (s + 1) * SZ < len)
+                        gather(x1, ids_cur, s + 1);
+                    count(x0, b, s);
+                    if (s + 2 < SPB) {
+                        if (b + (s + 2) * SZ < len)
+                            gather(x0, ids_cur, s + 2);
+                    } else if (b + kWave < len) {
+                        gather(x0, ids_nxt, 0);
+                    }
+                    count(x1, b, s + 1);
+                }
+            }
+            finish(b);
+            ids_cur = ids_nxt;
+            ids_nxt = ids_new;
+        };
+        if constexpr (SPB == 1) {
+            for (uint32_t b = 0; b < len; b += 2 * kWave) {
+                block(b, v0, v1);
+                if (b + kWave < len)
+                    block(b + kWave, v1, v0);
+            }
+        } else {
+            for (uint32_t b = 0; b < len; b += kWave)
+                block(b, v0, v1);
         }
-        wave_fence();
-        const uint32_t nwords = (uint32_t)((t1 - t0 + 31) >> 5);
-        for (uint32_t i = lane; i < nwords; i += kWave)
-            a.pass_bits[(t0 >> 5) + i] = tmask[i];
-        wave_fence();
+        ticket = uniform_u32(__shfl(drawn, 0)) * kTicketCounters + shard;
     }
 }
 
@@ -420,7 +708,12 @@ __global__ __launch_bounds__(64) void filter_plain_kernel(FilterArgs a)
 }
 
 // ---------------------------------------------------------------- dispatch
-#define GRIM_V(Q, G, U) {Q, G, U, reinterpret_cast<const void *>(&filter_batched_kernel<Q, G, U>)}
+// (lanes per candidate, unroll) as the tuning names them, and the kernel that
+// runs them.  A wave step holds 64 / G x U pairs and cannot pass the block of 64
+// whose outputs leave together, so an unroll above G runs the G-unrolled kernel
+// (which keeps the next step's loads in flight anyway).
+#define GRIM_V(Q, G, U)                                                                          \
+    {Q, G, U, reinterpret_cast<const void *>(&filter_batched_kernel<Q, G, (U < G ? U : G)>)}
 static const BatchedVariant kBatched[] = {
     GRIM_V(4, 2, 2),  GRIM_V(4, 2, 4),  GRIM_V(4, 2, 8),  GRIM_V(4, 1, 8),
     GRIM_V(5, 8, 1),  GRIM_V(5, 8, 2),  GRIM_V(5, 8, 4),  GRIM_V(5, 8, 8),
@@ -462,13 +755,13 @@ hipError_t launch_build(int q, dim3 grid, hipStream_t s, const uint32_t *ref, ui
     return hipGetLastError();
 }
 
-hipError_t launch_worklist(hipStream_t s, const uint64_t *cand_off, uint64_t n_reads,
-                           uint32_t tile_pairs, uint32_t n_tiles, uint32_t *tile_read,
-                           uint32_t *status, uint32_t *counter)
+hipError_t launch_worklist(hipStream_t s, const FilterArgs &a, uint32_t n_waves)
 {
-    const uint32_t blocks = n_tiles ? (n_tiles + 255) / 256 : 1;
-    hipLaunchKernelGGL(worklist_kernel, dim3(blocks), dim3(256), 0, s, cand_off, n_reads,
-                       tile_pairs, n_tiles, tile_read, status, counter);
+    const uint32_t n_table = a.ticket_read ? a.n_tickets : 0u;
+    const uint32_t blocks = n_table ? (n_table + 255) / 256 : 1;
+    hipLaunchKernelGGL(worklist_kernel, dim3(blocks), dim3(256), 0, s, a.cand_off, a.n_reads,
+                       n_table, a.n_big, a.big_pairs, a.small_pairs, n_waves,
+                       const_cast<uint32_t *>(a.ticket_read), a.status, a.counters);
     return hipGetLastError();
 }
 
