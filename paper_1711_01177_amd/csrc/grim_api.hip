@@ -343,6 +343,7 @@ extern "C" int grim_build_bins(const uint32_t *ref_2bit, uint64_t ref_len, const
     if (!idx)
         return GRIM_E_NOMEM;
     idx->d_ref = nullptr;
+    idx->d_planes = nullptr;
     idx->ref_words = 0;
     idx->d_rows = nullptr;
     idx->row_words = 0;
@@ -510,6 +511,7 @@ extern "C" int grim_index_load(const char *path, grim_index_t **out, void *strea
     if (!idx)
         return GRIM_E_NOMEM;
     idx->d_ref = nullptr;
+    idx->d_planes = nullptr;
     idx->ref_words = 0;
     idx->d_rows = nullptr;
     idx->row_words = 0;
@@ -544,6 +546,8 @@ extern "C" void grim_index_free(grim_index_t *idx)
         return;
     if (idx->d_ref)
         (void)hipFree(idx->d_ref);
+    if (idx->d_planes)
+        (void)hipFree(idx->d_planes);
     if (idx->d_rows)
         (void)hipFree(idx->d_rows);
     (void)hipFree(idx->d_vec);
@@ -823,22 +827,39 @@ extern "C" int grim_index_attach_reference(grim_index_t *idx, const uint32_t *re
     if (!idx || !ref_2bit || ref_len != idx->G)
         return GRIM_E_INVALID;
     const uint64_t nw = grim_packed_words(ref_len);
+    const uint64_t n_planes = (nw + 1) / 2 + 2 * kPlanePad;
     uint32_t *d = nullptr;
+    uint2 *planes = nullptr;
     if (hipMalloc(&d, (nw + kRefPadWords) * 4) != hipSuccess)
         return GRIM_E_NOMEM;
+    if (hipMalloc(&planes, n_planes * 8) != hipSuccess) {
+        (void)hipFree(d);
+        return GRIM_E_NOMEM;
+    }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = hipMemcpyAsync(d, ref_2bit, nw * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = launch_zero(s, d + nw, kRefPadWords);
     if (e == hipSuccess)
+        e = launch_zero(s, reinterpret_cast<uint32_t *>(planes), 2 * kPlanePad);
+    if (e == hipSuccess)
+        e = launch_zero(s, reinterpret_cast<uint32_t *>(planes + n_planes - kPlanePad),
+                        2 * kPlanePad);
+    if (e == hipSuccess)
+        e = launch_planes(s, d, nw, planes + kPlanePad);
+    if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(d);
+        (void)hipFree(planes);
         return hip_fail(e, "grim_index_attach_reference");
     }
     if (idx->d_ref)
         (void)hipFree(idx->d_ref);
+    if (idx->d_planes)
+        (void)hipFree(idx->d_planes);
     idx->d_ref = d;
+    idx->d_planes = planes;
     idx->ref_words = nw;
     return GRIM_OK;
 }
@@ -865,6 +886,7 @@ extern "C" int grim_verify_survivors(const grim_index_t *idx, const grim_batch_t
     std::memset(&a, 0, sizeof(a));
     a.ref = idx->d_ref;
     a.ref_words = idx->ref_words;
+    a.planes = idx->d_planes + kPlanePad;
     a.G = idx->G;
     a.B = idx->B;
     a.O = idx->O;

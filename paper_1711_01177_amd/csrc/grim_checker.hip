@@ -372,81 +372,436 @@ __device__ __forceinline__ int32_t column_scan_from(int s, const uint64_t *peq_t
     return column_scan<NW, S, UNI>(peq_t, pv, mv, rp, wsh, span, L);
 }
 
-// Each workgroup owns one contiguous range of survivors: one chunk of 1024,
-// or a run of whole chunks once the list exceeds 64 times the workgroups the
-// GPU holds at once (ranges start on multiples of 32, so that no two
-// workgroups share a word of pass bits).  It takes its range 1024 survivors
-// at a time, sorts them by the number of 32-row words of their read
-// (counting sort in LDS; survivors with nothing to align first, empty slots
-// of a short last chunk last) and runs the sorted list in four rounds of
-// 256, thread t taking sorted slot 256 r + t: a wavefront's 64 lanes then
-// mostly hold reads of one length class, and every wavefront meets short and
-// long reads over the four rounds, so none waits long for the others at the
-// chunk's end.  Pass bits of the chunk are gathered in LDS and stored as
-// whole words.  W is the number of 64-row blocks (NW = 2 W words) the
-// batch's longest read needs.
-constexpr int kVerifyChunk = 1024;
+// ------------------------------------------- location check by exact pieces
+// A read of L bases aligned with at most E edits, cut into E + 1 disjoint
+// pieces, has one that no edit touches: it occurs unchanged in the span, and the
+// whole alignment stays within E diagonals of it (R. Baeza-Yates and C. Perleberg,
+// 1992; the pigeonhole principle).  So the scan of all columns is needed only
+// where it could matter:
+//   A  every survivor's pieces are looked for in its span, by their first
+//      kPieceBases bases (E + 1 of them against 160 span positions at a time);
+//      a survivor without any is farther than E, and done;
+//   B  around the diagonals that were hit, a band of 32 or 64 diagonals is
+//      computed row by row of the read (the bit-parallel recurrence again, the
+//      vector now along the reference and sliding with the diagonal: H. Hyyro,
+//      2003), which gives the distance exactly if it is at most E;
+//   C  survivors whose pieces would be shorter than kPieceMin bases (chance hits
+//      would be everywhere) or more than kPieces, and those hit all over their
+//      span with too many edits to band it, take the scan of all columns below.
+//
+// The vector ALUs bound it: 2.5M survivors of 100-250 bases at 5-10 % edits take
+// 3.9e8 wavefront instructions (1.06e9 with the scan of all columns for each)
+// and 0.74 ms (1.64), 0.49 of it phase A; 18k survivors 0.16 ms (0.41).
+constexpr int kPieces = 32;          // pieces at most (E <= 31: two bands of E fit 64 diagonals)
+constexpr int kPieceMin = 8;         // bases of a piece at least
+constexpr int kPieceBases = 9;       // bases looked for (8 where a lane's pieces have no more)
+constexpr int kGroup = 5;            // 32-position words of the span taken together
+constexpr int64_t kSpanMax = 30000;  // diagonals are kept in 22 bits with their slot
+constexpr int kBandsPerRead = 64;    // bands for a read whose pieces hit far apart
 
-template <int W>
-__global__ __launch_bounds__(256) void verify_kernel(VerifyArgs a)
+__device__ __forceinline__ uint32_t lane_max(uint32_t x)
+{
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1)
+        x = max(x, (uint32_t)__shfl_xor(x, s));
+    return __builtin_amdgcn_readfirstlane(x);
+}
+
+// The n lowest bits (none for n <= 0, all for n >= 32).
+__device__ __forceinline__ uint32_t low_bits(int32_t n)
+{
+    return n >= 32 ? ~0u : n <= 0 ? 0u : (1u << n) - 1u;
+}
+
+constexpr uint32_t kOrXor = (0xF0u | (0xCCu ^ 0xAAu)) & 0xFFu;   // a | (b ^ c)
+
+// Phase A for one wave.  piece: this thread's pieces in LDS (256 threads apart,
+// first base in the top bits); np, m: their number and length (np = 0: lane
+// idle); p: the span's first reference word pair, sh its first base's bit;
+// np_max, span_max: the wave's largest.  [lo, hi] holds the diagonals (span
+// position minus read position) of every hit; lo > hi without one.
+//
+// Cost: the span's 160 positions are held as bit planes of the two code bits,
+// shifted by 0 .. 8 positions (90 registers, built once per group of words);
+// a piece then takes one v_bitop3 per base, code bit and word, and one
+// v_bfe_i32 per base and code bit that broadcasts the piece's own bit: 108
+// instructions per piece and 160 positions.
+__device__ __forceinline__ void find_pieces(const uint32_t *piece, uint32_t np, uint32_t m,
+                                            uint32_t np_max, bool nine, const uint2 *p,
+                                            uint32_t sh, int32_t span, int32_t span_max,
+                                            int32_t &lo, int32_t &hi)
+{
+    constexpr int K = kPieceBases;
+    lo = 0x3fffffff;
+    hi = -0x3fffffff;
+    const int bases = nine ? K : K - 1;
+    for (int32_t at = 0; at + bases <= span_max; at += 32 * kGroup) {
+        uint32_t th[kGroup + 1], tl[kGroup + 1];
+        {
+            uint2 w[kGroup + 2];
+#pragma unroll
+            for (int i = 0; i < kGroup + 2; ++i)
+                w[i] = p[(at >> 5) + i];
+#pragma unroll
+            for (int i = 0; i <= kGroup; ++i) {
+                th[i] = __builtin_amdgcn_alignbit(w[i + 1].x, w[i].x, sh);
+                tl[i] = __builtin_amdgcn_alignbit(w[i + 1].y, w[i].y, sh);
+            }
+        }
+        uint32_t hs[K][kGroup], ls[K][kGroup], out[kGroup];
+#pragma unroll
+        for (int w = 0; w < kGroup; ++w) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                hs[j][w] = j ? __builtin_amdgcn_alignbit(th[w + 1], th[w], j) : th[w];
+                ls[j][w] = j ? __builtin_amdgcn_alignbit(tl[w + 1], tl[w], j) : tl[w];
+            }
+            // positions too close to the span's end
+            out[w] = ~low_bits(span - bases + 1 - at - 32 * w);
+        }
+        for (uint32_t i = 0; i < np_max; ++i) {
+            const int32_t win = (int32_t)piece[i * 256];
+            uint32_t miss[kGroup];
+#pragma unroll
+            for (int w = 0; w < kGroup; ++w)
+                miss[w] = out[w];
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) {
+                const uint32_t bh = (win << (2 * j)) >> 31, bl = (win << (2 * j + 1)) >> 31;
+#pragma unroll
+                for (int w = 0; w < kGroup; ++w) {
+                    miss[w] = bitop3<kOrXor>(miss[w], hs[j][w], bh);
+                    miss[w] = bitop3<kOrXor>(miss[w], ls[j][w], bl);
+                }
+            }
+            if (nine) {
+                const uint32_t bh = (win << (2 * K - 2)) >> 31, bl = (win << (2 * K - 1)) >> 31;
+#pragma unroll
+                for (int w = 0; w < kGroup; ++w) {
+                    miss[w] = bitop3<kOrXor>(miss[w], hs[K - 1][w], bh);
+                    miss[w] = bitop3<kOrXor>(miss[w], ls[K - 1][w], bl);
+                }
+            }
+            uint32_t all = miss[0];
+#pragma unroll
+            for (int w = 1; w < kGroup; ++w)
+                all &= miss[w];
+            if (all != ~0u && i < np) {
+                // first and last hit of the group (a word without one saturates)
+                uint32_t a = ~0u, z = 0u;
+#pragma unroll
+                for (int w = 0; w < kGroup; ++w) {
+                    const uint32_t x = ~miss[w];
+                    a = min(a, __builtin_elementwise_add_sat((uint32_t)(__ffs(x) - 1), 32u * w));
+                    z = max(z, __builtin_elementwise_sub_sat(
+                                   32u * w + 31u, x ? (uint32_t)__builtin_clz(x) : ~0u));
+                }
+                const int32_t base = at - (int32_t)(i * m);
+                const int32_t first = base + (int32_t)a, last = base + (int32_t)z;
+                lo = min(lo, first);
+                hi = max(hi, last);
+            }
+        }
+    }
+}
+
+// Phase B for one wave: smallest distance of the lane's read (L bases at `off`)
+// to any substring of its span, over the alignments inside the NB * 32 diagonals
+// from dlo on; never less than the true smallest distance.  p: first reference
+// word pair of the whole array's base 0; lo: the span's first base.
+//
+// Row i, bit b is the cell (i, i + dlo + b); Pv/Mv hold the differences along
+// the row, aligned for the next row.  Positions outside the span match nothing,
+// which costs the same edits as the span's edge does.  Per row and 32 diagonals,
+// with Eq the matches of the row's base:
+//   D0 = (((Eq & Pv) + Pv) ^ Pv) | Eq | Mv   (equal to its diagonal neighbour)
+//   Hp = Mv | ~(D0 | Pv);  Hn = Pv & D0;  X = D0 >> 1
+//   Pv = Hn | ~(X | Hp);   Mv = X & Hp
+// about 17 instructions (33 for 64 diagonals), no memory but a word pair every
+// 32 rows and a read word every 16.
+template <int NB>
+__device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t dlo, int32_t span,
+                                             const uint32_t *__restrict__ rw, uint64_t nw,
+                                             uint64_t off, int32_t L)
+{
+    const int64_t t0 = lo + dlo;                     // reference position of row 0, bit 0
+    const uint2 *q = p + (t0 >> 5);                  // floor, also for negative positions
+    const uint32_t sh = (uint32_t)t0 & 31u;
+    uint32_t th[NB + 1], tl[NB + 1], tv[NB + 1];     // aligned words, and which positions count
+    uint2 raw = q[0];
+    auto fetch = [&](int n, int slot) {
+        const uint2 nx = q[n + 1];
+        th[slot] = __builtin_amdgcn_alignbit(nx.x, raw.x, sh);
+        tl[slot] = __builtin_amdgcn_alignbit(nx.y, raw.y, sh);
+        raw = nx;
+        const int32_t x = dlo + 32 * n;
+        tv[slot] = low_bits(span - x) & ~low_bits(-x);
+    };
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+        fetch(n, n);
+    uint32_t pv[NB], mv[NB];
+#pragma unroll
+    for (int w = 0; w < NB; ++w)
+        pv[w] = mv[w] = 0u;
+    int32_t s = L;
+    int32_t win = 0;
+    for (int32_t i = 0; i < L; ++i) {
+        const uint32_t k = (uint32_t)i & 31u;
+        if (k == 0) {
+            if (i) {
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    th[n] = th[n + 1];
+                    tl[n] = tl[n + 1];
+                    tv[n] = tv[n + 1];
+                }
+            }
+            fetch((i >> 5) + NB, NB);
+        }
+        if ((k & 15u) == 0)
+            win = (int32_t)read_window(rw, nw, (int64_t)off + i);
+        const uint32_t bh = win >> 31, bl = (win << 1) >> 31;
+        win <<= 2;
+        uint32_t eq[NB], d0[NB], c = 0;
+#pragma unroll
+        for (int w = 0; w < NB; ++w) {
+            const uint32_t a = __builtin_amdgcn_alignbit(th[w + 1], th[w], k);
+            const uint32_t b = __builtin_amdgcn_alignbit(tl[w + 1], tl[w], k);
+            const uint32_t v = __builtin_amdgcn_alignbit(tv[w + 1], tv[w], k);
+            const uint32_t ne = (b ^ bl) | ~v;
+            eq[w] = ~((a ^ bh) | ne);
+            const uint32_t sm = __builtin_addc(eq[w] & pv[w], pv[w], c, &c);
+            d0[w] = bitop3<kXorOr>(sm, pv[w], eq[w] | mv[w]);
+        }
+        s -= (int32_t)(d0[0] & 1u);
+#pragma unroll
+        for (int w = 0; w < NB; ++w) {
+            const uint32_t x = w + 1 < NB ? __builtin_amdgcn_alignbit(d0[w + 1 < NB ? w + 1 : w], d0[w], 1)
+                                          : d0[w] >> 1;
+            const uint32_t hp = bitop3<kOrNor>(mv[w], d0[w], pv[w]);
+            const uint32_t hn = pv[w] & d0[w];
+            pv[w] = bitop3<kOrNor>(hn, x, hp);
+            mv[w] = x & hp;
+        }
+    }
+    // s is the last row's cell on the lowest diagonal; the others by the row's
+    // differences
+    int32_t best = s;
+#pragma unroll
+    for (int w = 0; w < NB; ++w) {
+#pragma unroll
+        for (int b = 0; b < 32; ++b) {
+            if (w == NB - 1 && b == 31)
+                break;
+            s += (int32_t)((pv[w] >> b) & 1u) - (int32_t)((mv[w] >> b) & 1u);
+            best = min(best, s);
+        }
+    }
+    return best;
+}
+
+// Each workgroup owns one contiguous range of survivors: one chunk of CH, or a
+// run of whole chunks once the list exceeds 64 times the workgroups the GPU
+// holds at once (ranges start on multiples of 32, so that no two workgroups
+// share a word of pass bits).  It takes its range CH survivors at a time and
+// sorts them (counting sort in LDS): those whose pieces are looked for by their
+// tolerated edits, as many pieces as that takes, then the others by the number
+// of 32-row words of their read, empty slots of a short last chunk last.  Phase
+// A runs over the first part, 256 sorted slots at a time; phase B over the list
+// of bands it leaves (narrow ones from the front, wide ones from the back, so
+// that a wavefront has one kind), phase C over the second part and the few
+// survivors A could not settle.  A survivor's smallest distance is collected in
+// LDS as twice the distance, or 2 E + 1 while none within E is known; distances
+// and pass bits leave together.  W is the number of 64-row blocks (NW = 2 W
+// words) the batch's longest read needs.
+constexpr int kVerifyChunk = 1024;
+constexpr int kVerifySmall = 256;
+
+template <int W, int CH>
+__global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a)
 {
     constexpr int NW = 2 * W;
-    constexpr int CH = kVerifyChunk;
+    constexpr int kKeys = kPieces + NW + 2;   // edits | words | past the chunk's end
+    constexpr uint32_t kSettled = ~0u;        // written to memory already
+    constexpr uint32_t kBands = CH + CH / 2;
+    static_assert(kKeys <= 64, "one wavefront scans the keys");
     __shared__ uint16_t order[CH];
-    __shared__ uint32_t cls[NW + 2];
+    __shared__ uint32_t cls[64];
     __shared__ uint32_t okw[CH / 32];
-    // match masks of every thread's read: peq[(base * W + block) * 256 + thread],
-    // block = rows 64 block .. 64 block + 63 of the bottom-aligned vector
-    // (lane-interleaved, so that a wavefront's reads of one column are
-    // conflict-free whatever bases its lanes see)
-    __shared__ uint64_t peq[4 * W * 256];
-    const int t = threadIdx.x;
+    __shared__ uint32_t best[CH];
+    // bands to compute: slot in the low 10 bits, first diagonal + 8192 above
+    __shared__ uint32_t bands[kBands];
+    __shared__ uint16_t rest[CH];             // survivors of phase A for phase C
+    __shared__ uint32_t n_bands, n_narrow, n_wide, n_rest;
+    __shared__ uint32_t next_a, next_b;       // wavefront runs of phases A and B handed out
+    // phase A: pieces[piece * 256 + thread]; phase C: the match masks of every
+    // thread's read, peq[(base * W + block) * 256 + thread], block = rows 64
+    // block .. 64 block + 63 of the bottom-aligned vector (lane-interleaved, so
+    // that a wavefront's reads of one column are conflict-free whatever bases
+    // its lanes see)
+    __shared__ uint64_t peq[(W > 4 ? 4 * W : 16) * 256];
+    uint32_t *pieces = reinterpret_cast<uint32_t *>(peq);
+    const int t = threadIdx.x, lane = t & 63;
+    auto draw = [&](uint32_t *next) -> uint32_t {
+        uint32_t x = 0;
+        if (lane == 0)
+            x = atomicAdd(next, 1u);
+        return __builtin_amdgcn_readfirstlane(x);
+    };
+    const uint64_t nb = a.nw * 16;
     const uint64_t per = ((a.n_surv + gridDim.x - 1) / gridDim.x + 31) & ~31ull;
     const uint64_t g0 = (uint64_t)blockIdx.x * per;
     const uint64_t g1 = g0 + per < a.n_surv ? g0 + per : a.n_surv;
+    auto span_of = [&](uint64_t lo) -> uint64_t {
+        uint64_t hi = lo + a.B + a.O;
+        if (hi > a.G)
+            hi = a.G;
+        return hi > lo ? hi - lo : 0;
+    };
+    // the longest span, in 32 bits: batches with longer ones have no survivor
+    // in phases A and B
+    const uint64_t span_all = a.B + a.O < a.G ? a.B + a.O : a.G;
     for (uint64_t base = g0; base < g1; base += CH) {
         const uint32_t cnt = (uint32_t)(g1 - base < (uint64_t)CH ? g1 - base : CH);
-        if (t < NW + 2)
+        if (t < 64)
             cls[t] = 0;
         if (t < CH / 32)
             okw[t] = 0;
+        if (t == 0)
+            n_bands = n_narrow = n_wide = n_rest = next_a = next_b = 0;
         __syncthreads();
-        // class of slot u 256 + t: its read's word count, 0 when there is
-        // nothing to align, NW + 1 past the chunk's end
+        // class of slot u 256 + t
         int key[CH / 256];
         uint32_t rank[CH / 256];
 #pragma unroll
         for (int u = 0; u < CH / 256; ++u) {
             const uint32_t p = u * 256 + t;
-            int k = NW + 1;
+            int k = kKeys - 1;
             if (p < cnt) {
-                k = 0;
-                const uint32_t r = a.surv_read[base + p];
+                k = kPieces;
+                const uint32_t r = a.surv_read[base + p], b = a.surv_bin[base + p];
                 if (r < a.n_reads) {
                     const uint32_t L = a.read_len[r];
-                    k = L <= 32u * NW ? (int)((L + 31) >> 5) : 0;
+                    if (L <= 32u * NW)
+                        k = kPieces + (int)((L + 31) >> 5);
+                    const uint64_t off = a.read_off[r];
+                    const uint64_t E = ((uint64_t)a.read_e[r] * L + a.e_den - 1) / a.e_den;
+                    if (b < a.n_bins && L <= 32u * NW && off <= nb && L <= nb - off &&
+                        E < (uint64_t)kPieces && L >= (E + 1) * kPieceMin &&
+                        span_all <= (uint64_t)kSpanMax) {
+                        k = (int)E;
+                        best[p] = 2 * (uint32_t)E + 1;   // more than E
+                    }
                 }
             }
             key[u] = k;
             rank[u] = atomicAdd(&cls[k], 1u);
         }
         __syncthreads();
+        if (t < 64) {   // first slot of every class
+            const uint32_t n = cls[t];
+            uint32_t before = n;
 #pragma unroll
-        for (int u = 0; u < CH / 256; ++u) {
-            uint32_t start = 0;
-            for (int c = 0; c < key[u]; ++c)
-                start += cls[c];
-            order[start + rank[u]] = (uint16_t)(u * 256 + t);
+            for (int s = 1; s < 64; s <<= 1) {
+                const uint32_t y = __shfl_up(before, s);
+                if (t >= s)
+                    before += y;
+            }
+            cls[t] = before - n;
         }
         __syncthreads();
-        for (int round = 0; round < CH / 256; ++round) {
-            const uint32_t slot = order[round * 256 + t];
+#pragma unroll
+        for (int u = 0; u < CH / 256; ++u)
+            order[cls[key[u]] + rank[u]] = (uint16_t)(u * 256 + t);
+        const uint32_t n_pieces = cls[kPieces];   // survivors of phase A
+        __syncthreads();
+
+        // ------------------------------------------------ phase A: pieces
+        for (;;) {
+            const uint32_t at = draw(&next_a);
+            if (at * kWave >= n_pieces)
+                break;
+            const uint32_t x0 = ((n_pieces - 1) / kWave - at) * kWave;   // most pieces first
+            const bool on = x0 + lane < n_pieces;
+            const uint32_t slot = order[on ? x0 + lane : x0];
+            const uint32_t r = a.surv_read[base + slot], b = a.surv_bin[base + slot];
+            const int32_t L = (int32_t)a.read_len[r];
+            const uint64_t off = a.read_off[r];
+            const int32_t E = (int32_t)(best[slot] >> 1);
+            const uint32_t m = (uint32_t)L / (uint32_t)(E + 1);
+            const uint32_t np = on ? (uint32_t)E + 1 : 0u;
+            const uint32_t np_max = lane_max(np);
+            const bool nine = __builtin_amdgcn_ballot_w64(m < kPieceBases) == 0;
+            for (uint32_t i = 0; i < np_max; ++i)
+                pieces[i * 256 + t] = i < np ? read_window(a.rw, a.nw, (int64_t)(off + i * m)) : 0u;
+            const uint64_t lo = (uint64_t)b * a.B;
+            const int32_t span = (int32_t)span_of(lo);
+            int32_t h0, h1;
+            find_pieces(pieces + t, np, m, np_max, nine, a.planes + (lo >> 5), (uint32_t)lo & 31u,
+                        span, (int32_t)span_all, h0, h1);
+            if (on && h0 <= h1) {
+                auto push = [&](int32_t first, bool narrow) -> bool {
+                    if (atomicAdd(&n_bands, 1u) >= kBands)
+                        return false;
+                    const uint32_t at = narrow ? atomicAdd(&n_narrow, 1u)
+                                               : kBands - 1 - atomicAdd(&n_wide, 1u);
+                    bands[at] = slot | (uint32_t)(first - E + 8192) << 10;
+                    return true;
+                };
+                // one band where the hits lie together (nearly always), else as
+                // many as it takes to cover all of them
+                const int32_t step = 64 - 2 * E;   // diagonals a wide band settles
+                const int32_t n = (h1 - h0) / step + 1;
+                bool done = n <= kBandsPerRead;
+                for (int32_t i = 0; done && i < n; ++i)
+                    done = push(h0 + i * step, h1 - h0 < 32 - 2 * E);
+                if (!done) {
+                    rest[atomicAdd(&n_rest, 1u)] = (uint16_t)slot;
+                    best[slot] = kSettled;
+                }
+            }
+        }
+        __syncthreads();
+
+        // ------------------------------------------------- phase B: bands
+        const uint32_t nn = n_narrow, nw2 = n_wide;
+        const uint32_t nw64 = (nw2 + kWave - 1) / kWave * kWave;
+        for (;;) {
+            const uint32_t x0 = draw(&next_b) * kWave;   // wide ones first
+            if (x0 >= nw64 + nn)
+                break;
+            const bool narrow = x0 >= nw64;
+            const uint32_t x = narrow ? x0 - nw64 + lane : x0 + lane;
+            if (x < (narrow ? nn : nw2)) {
+                const uint32_t e = bands[narrow ? x : kBands - 1 - x];
+                const uint32_t slot = e & 1023u;
+                const int32_t dlo = (int32_t)(e >> 10) - 8192;
+                const uint32_t v = best[slot];
+                if (v != kSettled) {
+                    const uint32_t r = a.surv_read[base + slot], b = a.surv_bin[base + slot];
+                    const int32_t L = (int32_t)a.read_len[r];
+                    const uint64_t off = a.read_off[r];
+                    const int64_t lo = (int64_t)((uint64_t)b * a.B);
+                    const int32_t span = (int32_t)span_of((uint64_t)lo);
+                    const int32_t d =
+                        narrow ? band_scan<1>(a.planes, lo, dlo, span, a.rw, a.nw, off, L)
+                               : band_scan<2>(a.planes, lo, dlo, span, a.rw, a.nw, off, L);
+                    atomicMin(&best[slot], 2u * (uint32_t)d);
+                }
+            }
+        }
+        __syncthreads();
+
+        // --------------------------------------------- phase C: all columns
+        const uint32_t n_all = cls[kKeys - 1] - n_pieces;   // survivors without pieces
+        for (uint32_t x = t; x < n_all + n_rest; x += 256) {
+            const uint32_t slot = x < n_all ? order[n_pieces + x] : rest[x - n_all];
             const uint64_t i = base + slot;
-            if (slot < cnt) {
+            {
                 int32_t d = -1;
                 bool ok = false;
                 const uint32_t r = a.surv_read[i], b = a.surv_bin[i];
-                const uint64_t nb = a.nw * 16;
                 const uint32_t L = r < a.n_reads ? a.read_len[r] : 0u;
                 const uint64_t off = r < a.n_reads ? a.read_off[r] : 0u;
                 if (r < a.n_reads && b < a.n_bins && L <= 32u * NW && off <= nb &&
@@ -530,6 +885,16 @@ __global__ __launch_bounds__(256) void verify_kernel(VerifyArgs a)
                     atomicOr(&okw[slot >> 5], 1u << (slot & 31));
             }
         }
+        // distances of phases A and B
+        for (uint32_t x = t; x < n_pieces; x += 256) {
+            const uint32_t slot = order[x];
+            const uint32_t v = best[slot];
+            if (v != kSettled) {
+                a.dist[base + slot] = (int32_t)((v + 1) >> 1);
+                if (!(v & 1u))
+                    atomicOr(&okw[slot >> 5], 1u << (slot & 31));
+            }
+        }
         __syncthreads();
         if (t < (int)((cnt + 31) / 32))
             a.ok_bits[(base >> 5) + t] = okw[t];
@@ -537,22 +902,55 @@ __global__ __launch_bounds__(256) void verify_kernel(VerifyArgs a)
     }
 }
 
+// Splits the packed reference into bit planes: word pair j holds the high (x) and
+// low (y) code bits of bases 32 j .. 32 j + 31, the first in bit 0.
+__global__ __launch_bounds__(256) void planes_kernel(const uint32_t *__restrict__ ref, uint64_t nw,
+                                                     uint64_t n_pairs, uint2 *__restrict__ out)
+{
+    const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= n_pairs)
+        return;
+    const uint32_t r0 = __builtin_bitreverse32(ref[2 * j]);   // 2 j < nw
+    const uint32_t r1 = __builtin_bitreverse32(2 * j + 1 < nw ? ref[2 * j + 1] : 0u);
+    out[j] = make_uint2(even_bits(r0 & 0x55555555u) | even_bits(r1 & 0x55555555u) << 16,
+                        even_bits((r0 >> 1) & 0x55555555u) |
+                            even_bits((r1 >> 1) & 0x55555555u) << 16);
+}
+
+hipError_t launch_planes(hipStream_t s, const uint32_t *ref, uint64_t nw, uint2 *planes)
+{
+    const uint64_t n_pairs = (nw + 1) / 2;
+    if (n_pairs)
+        hipLaunchKernelGGL(planes_kernel, dim3((uint32_t)((n_pairs + 255) / 256)), dim3(256), 0, s,
+                           ref, nw, n_pairs, planes);
+    return hipGetLastError();
+}
+
 hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a)
 {
     VerifyArgs copy = a;
     void *args[] = {&copy};
+    // chunks of 1024 sort and pack better (512: 9 % slower on 2.5M survivors);
+    // short lists, which would leave CUs without a workgroup, take chunks of 256
+    const bool small = a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * 2 * kVerifyChunk;
+    const uint64_t chunk = small ? kVerifySmall : kVerifyChunk;
     const void *k = nullptr;
     int wi = 0;
+#define VERIFY_K(W)                                                                \
+    (small ? reinterpret_cast<const void *>(&verify_kernel<W, kVerifySmall>)       \
+           : reinterpret_cast<const void *>(&verify_kernel<W, kVerifyChunk>))
     switch (W) {
-    case 1: k = reinterpret_cast<const void *>(&verify_kernel<1>); wi = 0; break;
-    case 2: k = reinterpret_cast<const void *>(&verify_kernel<2>); wi = 1; break;
-    case 4: k = reinterpret_cast<const void *>(&verify_kernel<4>); wi = 2; break;
-    case 8: k = reinterpret_cast<const void *>(&verify_kernel<8>); wi = 3; break;
+    case 1: k = VERIFY_K(1); wi = 0; break;
+    case 2: k = VERIFY_K(2); wi = 1; break;
+    case 4: k = VERIFY_K(4); wi = 2; break;
+    case 8: k = VERIFY_K(8); wi = 3; break;
     default: return hipErrorInvalidValue;
     }
+#undef VERIFY_K
+    wi = 2 * wi + small;
     // workgroups resident per CU (LDS bound), asked once per kernel and
     // process; it only sizes the grid's cap, never what is computed
-    static std::atomic<int> resident[4];
+    static std::atomic<int> resident[8];
     int per_cu = resident[wi].load(std::memory_order_relaxed);
     if (per_cu <= 0) {
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0);
@@ -564,7 +962,7 @@ hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a)
     }
     // one sorted chunk per workgroup, dispatched as resident ones finish;
     // past 64 times the resident count, each takes a run of m whole chunks
-    const uint64_t chunks = (a.n_surv + kVerifyChunk - 1) / kVerifyChunk;
+    const uint64_t chunks = (a.n_surv + chunk - 1) / chunk;
     const uint64_t cap = (uint64_t)per_cu * (uint64_t)(cus > 0 ? cus : 1) * 64;
     const uint64_t m = (chunks + cap - 1) / cap;
     const uint64_t grid = (chunks + m - 1) / m;

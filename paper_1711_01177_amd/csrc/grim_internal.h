@@ -50,11 +50,17 @@ struct FilterArgs {
 // Zero words kept after the packed reference for the alignment check, whose
 // look-ahead fetches of reference words run up to three words past the end.
 constexpr uint64_t kRefPadWords = 4;
+// Zero word pairs before and after the reference's bit planes: a band of 64
+// diagonals starts up to a read (512 bases) and its edits before its span and
+// ends as far past it, and the piece search fetches up to 12 pairs past a
+// span's first one.
+constexpr uint64_t kPlanePad = 64;
 
 // Arguments of the alignment-check kernel.
 struct VerifyArgs {
     const uint32_t *ref;        // packed reference, kRefPadWords zero words after its end
     uint64_t ref_words;
+    const uint2 *planes;        // bit planes of the reference, kPlanePad pairs around them
     uint64_t G, B, O, n_bins;
     const uint32_t *rw;
     uint64_t nw;
@@ -114,6 +120,7 @@ hipError_t launch_compact(hipStream_t s, const uint32_t *bits, uint64_t n_pairs,
                           uint64_t cap, uint64_t *surv_pair, uint32_t *surv_read,
                           uint32_t *surv_bin, uint64_t *n_out, uint64_t *block_sums);
 uint64_t compact_blocks(uint64_t n_pairs);
+hipError_t launch_planes(hipStream_t s, const uint32_t *ref, uint64_t nw, uint2 *planes);
 hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a);
 hipError_t launch_transpose(hipStream_t s, int q, const uint32_t *vec, uint64_t n_bins,
                             uint64_t row_words, uint32_t *rows, uint32_t grid);
@@ -150,6 +157,7 @@ struct grim_index {
     void *d_vec;
     uint32_t *d_ref;        // packed reference kept for alignment checks (or null),
                             // followed by kRefPadWords zero words
+    uint2 *d_planes;        // its bit planes, kPlanePad zero pairs before and after
     uint64_t ref_words;
     uint32_t *d_rows;       // token-major copy for the bin-window form (or null)
     uint64_t row_words;
