@@ -259,6 +259,17 @@ __device__ __forceinline__ uint32_t read_window(const uint32_t *__restrict__ w, 
     return (uint32_t)((((uint64_t)w0 << 32) | w1) >> (32 - sh));
 }
 
+// The same for a position inside the array, without branches: bases past the
+// array's end come out as anything.
+__device__ __forceinline__ uint32_t read_window_in(const uint32_t *__restrict__ w, uint64_t nw,
+                                                   uint64_t pos)
+{
+    const uint64_t wi = pos >> 4;
+    const uint32_t sh = (uint32_t)(pos & 15) << 1;
+    const uint32_t w0 = w[wi], w1 = w[wi + 1 < nw ? wi + 1 : wi];
+    return sh ? __builtin_amdgcn_alignbit(w0, w1, 32 - sh) : w0;
+}
+
 // Bits 0, 2, ..., 30 of x gathered into bits 0..15.
 __device__ __forceinline__ uint32_t even_bits(uint32_t x)
 {
@@ -381,7 +392,7 @@ __device__ __forceinline__ int32_t column_scan_from(int s, const uint64_t *peq_t
 //   A  every survivor's pieces are looked for in its span, by their first
 //      kPieceBases bases (E + 1 of them against 160 span positions at a time);
 //      a survivor without any is farther than E, and done;
-//   B  around the diagonals that were hit, a band of 32 or 64 diagonals is
+//   B  around the diagonals that were hit, a band of 32, 64 or 128 diagonals is
 //      computed row by row of the read (the bit-parallel recurrence again, the
 //      vector now along the reference and sliding with the diagonal: H. Hyyro,
 //      2003), which gives the distance exactly if it is at most E;
@@ -391,13 +402,12 @@ __device__ __forceinline__ int32_t column_scan_from(int s, const uint64_t *peq_t
 //
 // The vector ALUs bound it: 2.5M survivors of 100-250 bases at 5-10 % edits take
 // 3.9e8 wavefront instructions (1.06e9 with the scan of all columns for each)
-// and 0.74 ms (1.64), 0.49 of it phase A; 18k survivors 0.16 ms (0.41).
+// and 0.75 ms (1.64), 0.49 of it phase A; 7.4e4 survivors 0.12 ms (0.41).
 constexpr int kPieces = 32;          // pieces at most (E <= 31: two bands of E fit 64 diagonals)
 constexpr int kPieceMin = 8;         // bases of a piece at least
 constexpr int kPieceBases = 9;       // bases looked for (8 where a lane's pieces have no more)
 constexpr int kGroup = 5;            // 32-position words of the span taken together
 constexpr int64_t kSpanMax = 30000;  // diagonals are kept in 22 bits with their slot
-constexpr int kBandsPerRead = 64;    // bands for a read whose pieces hit far apart
 
 __device__ __forceinline__ uint32_t lane_max(uint32_t x)
 {
@@ -497,9 +507,8 @@ __device__ __forceinline__ void find_pieces(const uint32_t *piece, uint32_t np, 
                                    32u * w + 31u, x ? (uint32_t)__builtin_clz(x) : ~0u));
                 }
                 const int32_t base = at - (int32_t)(i * m);
-                const int32_t first = base + (int32_t)a, last = base + (int32_t)z;
-                lo = min(lo, first);
-                hi = max(hi, last);
+                lo = min(lo, base + (int32_t)a);
+                hi = max(hi, base + (int32_t)z);
             }
         }
     }
@@ -517,8 +526,8 @@ __device__ __forceinline__ void find_pieces(const uint32_t *piece, uint32_t np, 
 //   D0 = (((Eq & Pv) + Pv) ^ Pv) | Eq | Mv   (equal to its diagonal neighbour)
 //   Hp = Mv | ~(D0 | Pv);  Hn = Pv & D0;  X = D0 >> 1
 //   Pv = Hn | ~(X | Hp);   Mv = X & Hp
-// about 17 instructions (33 for 64 diagonals), no memory but a word pair every
-// 32 rows and a read word every 16.
+// about 17 instructions (33 for 64 diagonals, 65 for 128), no memory but a word
+// pair every 32 rows and a read word every 16.
 template <int NB>
 __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t dlo, int32_t span,
                                              const uint32_t *__restrict__ rw, uint64_t nw,
@@ -528,12 +537,14 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
     const uint2 *q = p + (t0 >> 5);                  // floor, also for negative positions
     const uint32_t sh = (uint32_t)t0 & 31u;
     uint32_t th[NB + 1], tl[NB + 1], tv[NB + 1];     // aligned words, and which positions count
-    uint2 raw = q[0];
+    // loads run one use ahead: the next word pair of the reference, the next word
+    // of the read (the last one again past its end)
+    uint2 raw = q[0], ahead = q[1];
     auto fetch = [&](int n, int slot) {
-        const uint2 nx = q[n + 1];
-        th[slot] = __builtin_amdgcn_alignbit(nx.x, raw.x, sh);
-        tl[slot] = __builtin_amdgcn_alignbit(nx.y, raw.y, sh);
-        raw = nx;
+        th[slot] = __builtin_amdgcn_alignbit(ahead.x, raw.x, sh);
+        tl[slot] = __builtin_amdgcn_alignbit(ahead.y, raw.y, sh);
+        raw = ahead;
+        ahead = q[n + 2];
         const int32_t x = dlo + 32 * n;
         tv[slot] = low_bits(span - x) & ~low_bits(-x);
     };
@@ -544,6 +555,11 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
 #pragma unroll
     for (int w = 0; w < NB; ++w)
         pv[w] = mv[w] = 0u;
+    const uint32_t *r = rw + (off >> 4);
+    const uint64_t r_last = nw - 1 - (off >> 4);
+    const uint32_t rsh = (uint32_t)(off & 15) << 1;
+    auto word = [&](uint64_t n) { return r[n < r_last ? n : r_last]; };
+    uint32_t c0 = word(0), c1 = word(1), c2 = word(2);
     int32_t s = L;
     int32_t win = 0;
     for (int32_t i = 0; i < L; ++i) {
@@ -559,8 +575,12 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
             }
             fetch((i >> 5) + NB, NB);
         }
-        if ((k & 15u) == 0)
-            win = (int32_t)read_window(rw, nw, (int64_t)off + i);
+        if ((k & 15u) == 0) {
+            win = (int32_t)(rsh ? __builtin_amdgcn_alignbit(c0, c1, 32 - rsh) : c0);
+            c0 = c1;
+            c1 = c2;
+            c2 = word((i >> 4) + 3);
+        }
         const uint32_t bh = win >> 31, bl = (win << 1) >> 31;
         win <<= 2;
         uint32_t eq[NB], d0[NB], c = 0;
@@ -624,16 +644,17 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
     constexpr int NW = 2 * W;
     constexpr int kKeys = kPieces + NW + 2;   // edits | words | past the chunk's end
     constexpr uint32_t kSettled = ~0u;        // written to memory already
-    constexpr uint32_t kBands = CH + CH / 2;
+    constexpr uint32_t kBands = CH + CH / 2, kBroad = W > 4 && CH > 256 ? 128 : 512;
+    constexpr int U = CH / 256;   // slots per thread
     static_assert(kKeys <= 64, "one wavefront scans the keys");
     __shared__ uint16_t order[CH];
     __shared__ uint32_t cls[64];
     __shared__ uint32_t okw[CH / 32];
     __shared__ uint32_t best[CH];
     // bands to compute: slot in the low 10 bits, first diagonal + 8192 above
-    __shared__ uint32_t bands[kBands];
+    __shared__ uint32_t bands[kBands], broad[kBroad];
     __shared__ uint16_t rest[CH];             // survivors of phase A for phase C
-    __shared__ uint32_t n_bands, n_narrow, n_wide, n_rest;
+    __shared__ uint32_t n_bands, n_narrow, n_wide, n_broad, n_rest;
     __shared__ uint32_t next_a, next_b;       // wavefront runs of phases A and B handed out
     // phase A: pieces[piece * 256 + thread]; phase C: the match masks of every
     // thread's read, peq[(base * W + block) * 256 + thread], block = rows 64
@@ -669,13 +690,13 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
         if (t < CH / 32)
             okw[t] = 0;
         if (t == 0)
-            n_bands = n_narrow = n_wide = n_rest = next_a = next_b = 0;
+            n_bands = n_narrow = n_wide = n_broad = n_rest = next_a = next_b = 0;
         __syncthreads();
         // class of slot u 256 + t
-        int key[CH / 256];
-        uint32_t rank[CH / 256];
+        int key[U];
+        uint32_t rank[U];
 #pragma unroll
-        for (int u = 0; u < CH / 256; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t p = u * 256 + t;
             int k = kKeys - 1;
             if (p < cnt) {
@@ -712,17 +733,44 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < CH / 256; ++u)
+        for (int u = 0; u < U; ++u)
             order[cls[key[u]] + rank[u]] = (uint16_t)(u * 256 + t);
         const uint32_t n_pieces = cls[kPieces];   // survivors of phase A
         __syncthreads();
 
         // ------------------------------------------------ phase A: pieces
+        // the bands of a survivor whose pieces hit on diagonals h0 .. h1: one
+        // where the hits lie together (nearly always), else as many of 128
+        // diagonals as it takes to cover all of them
+        auto settle = [&](uint32_t slot, int32_t E, int32_t h0, int32_t h1) {
+            auto entry = [&](int32_t first) { return slot | (uint32_t)(first - E + 8192) << 10; };
+            bool done = true;
+            if (h1 - h0 < 64 - 2 * E) {
+                done = atomicAdd(&n_bands, 1u) < kBands;
+                if (done) {
+                    const uint32_t at = h1 - h0 < 32 - 2 * E ? atomicAdd(&n_narrow, 1u)
+                                                             : kBands - 1 - atomicAdd(&n_wide, 1u);
+                    bands[at] = entry(h0);
+                }
+            } else {
+                const int32_t step = 128 - 2 * E;
+                for (; done && h0 <= h1; h0 += step) {
+                    const uint32_t at = atomicAdd(&n_broad, 1u);
+                    done = at < kBroad;
+                    if (done)
+                        broad[at] = entry(h0);
+                }
+            }
+            if (!done) {
+                rest[atomicAdd(&n_rest, 1u)] = (uint16_t)slot;
+                best[slot] = kSettled;
+            }
+        };
         for (;;) {
-            const uint32_t at = draw(&next_a);
-            if (at * kWave >= n_pieces)
+            const uint32_t run = draw(&next_a);
+            if (run * kWave >= n_pieces)
                 break;
-            const uint32_t x0 = ((n_pieces - 1) / kWave - at) * kWave;   // most pieces first
+            const uint32_t x0 = ((n_pieces - 1) / kWave - run) * kWave;   // most pieces first
             const bool on = x0 + lane < n_pieces;
             const uint32_t slot = order[on ? x0 + lane : x0];
             const uint32_t r = a.surv_read[base + slot], b = a.surv_bin[base + slot];
@@ -733,48 +781,32 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
             const uint32_t np = on ? (uint32_t)E + 1 : 0u;
             const uint32_t np_max = lane_max(np);
             const bool nine = __builtin_amdgcn_ballot_w64(m < kPieceBases) == 0;
+#pragma unroll 4
             for (uint32_t i = 0; i < np_max; ++i)
-                pieces[i * 256 + t] = i < np ? read_window(a.rw, a.nw, (int64_t)(off + i * m)) : 0u;
+                pieces[i * 256 + t] = read_window_in(a.rw, a.nw, off + (i < np ? i * m : 0u));
             const uint64_t lo = (uint64_t)b * a.B;
             const int32_t span = (int32_t)span_of(lo);
             int32_t h0, h1;
             find_pieces(pieces + t, np, m, np_max, nine, a.planes + (lo >> 5), (uint32_t)lo & 31u,
                         span, (int32_t)span_all, h0, h1);
-            if (on && h0 <= h1) {
-                auto push = [&](int32_t first, bool narrow) -> bool {
-                    if (atomicAdd(&n_bands, 1u) >= kBands)
-                        return false;
-                    const uint32_t at = narrow ? atomicAdd(&n_narrow, 1u)
-                                               : kBands - 1 - atomicAdd(&n_wide, 1u);
-                    bands[at] = slot | (uint32_t)(first - E + 8192) << 10;
-                    return true;
-                };
-                // one band where the hits lie together (nearly always), else as
-                // many as it takes to cover all of them
-                const int32_t step = 64 - 2 * E;   // diagonals a wide band settles
-                const int32_t n = (h1 - h0) / step + 1;
-                bool done = n <= kBandsPerRead;
-                for (int32_t i = 0; done && i < n; ++i)
-                    done = push(h0 + i * step, h1 - h0 < 32 - 2 * E);
-                if (!done) {
-                    rest[atomicAdd(&n_rest, 1u)] = (uint16_t)slot;
-                    best[slot] = kSettled;
-                }
-            }
+            if (on && h0 <= h1)
+                settle(slot, E, h0, h1);
         }
         __syncthreads();
 
         // ------------------------------------------------- phase B: bands
-        const uint32_t nn = n_narrow, nw2 = n_wide;
-        const uint32_t nw64 = (nw2 + kWave - 1) / kWave * kWave;
+        // runs of one kind, the longest first
+        const uint32_t n1 = n_narrow, n2 = n_wide, n4 = min(n_broad, kBroad);
+        const uint32_t end4 = (n4 + kWave - 1) / kWave * kWave;
+        const uint32_t end2 = end4 + (n2 + kWave - 1) / kWave * kWave;
         for (;;) {
-            const uint32_t x0 = draw(&next_b) * kWave;   // wide ones first
-            if (x0 >= nw64 + nn)
+            const uint32_t x0 = draw(&next_b) * kWave;
+            if (x0 >= end2 + n1)
                 break;
-            const bool narrow = x0 >= nw64;
-            const uint32_t x = narrow ? x0 - nw64 + lane : x0 + lane;
-            if (x < (narrow ? nn : nw2)) {
-                const uint32_t e = bands[narrow ? x : kBands - 1 - x];
+            const int kind = x0 < end4 ? 4 : x0 < end2 ? 2 : 1;
+            const uint32_t x = x0 + lane - (kind == 4 ? 0u : kind == 2 ? end4 : end2);
+            if (x < (kind == 4 ? n4 : kind == 2 ? n2 : n1)) {
+                const uint32_t e = kind == 4 ? broad[x] : bands[kind == 2 ? kBands - 1 - x : x];
                 const uint32_t slot = e & 1023u;
                 const int32_t dlo = (int32_t)(e >> 10) - 8192;
                 const uint32_t v = best[slot];
@@ -784,9 +816,13 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
                     const uint64_t off = a.read_off[r];
                     const int64_t lo = (int64_t)((uint64_t)b * a.B);
                     const int32_t span = (int32_t)span_of((uint64_t)lo);
-                    const int32_t d =
-                        narrow ? band_scan<1>(a.planes, lo, dlo, span, a.rw, a.nw, off, L)
-                               : band_scan<2>(a.planes, lo, dlo, span, a.rw, a.nw, off, L);
+                    int32_t d;
+                    if (kind == 1)
+                        d = band_scan<1>(a.planes, lo, dlo, span, a.rw, a.nw, off, L);
+                    else if (kind == 2)
+                        d = band_scan<2>(a.planes, lo, dlo, span, a.rw, a.nw, off, L);
+                    else
+                        d = band_scan<4>(a.planes, lo, dlo, span, a.rw, a.nw, off, L);
                     atomicMin(&best[slot], 2u * (uint32_t)d);
                 }
             }
@@ -930,9 +966,10 @@ hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a)
 {
     VerifyArgs copy = a;
     void *args[] = {&copy};
-    // chunks of 1024 sort and pack better (512: 9 % slower on 2.5M survivors);
-    // short lists, which would leave CUs without a workgroup, take chunks of 256
-    const bool small = a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * 2 * kVerifyChunk;
+    // chunks of 1024 sort and pack better (2.5M survivors: 512 9 % slower; 5.3e5:
+    // 246 us, 256 327 us); lists that would leave CUs without one take chunks of
+    // 256 (7.3e4: 121 us; 64, the wavefronts sharing each survivor's pieces, 144)
+    const bool small = a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * kVerifyChunk;
     const uint64_t chunk = small ? kVerifySmall : kVerifyChunk;
     const void *k = nullptr;
     int wi = 0;

@@ -75,7 +75,7 @@ def test_edits_around_the_tolerance(max_len, B, O):
 def test_pieces_that_hit_everywhere():
     """Tandem repeats and long runs: pieces hit on many diagonals (several bands
     of one read, lists of bands running full, the scan of all columns), in
-    chunks of both sizes."""
+    chunks of every size."""
     rng = np.random.default_rng(3)
     parts = []
     for unit in (1, 2, 3, 7, 13, 29, 61, 90):
@@ -95,4 +95,5 @@ def test_pieces_that_hit_everywhere():
         es.append(int(rng.choice([0, 300, 500, 1000, 1100, 2500])))
         bins.append([st // B, int(rng.integers(0, nb))])
     _check(ref, B, O, reads, es, bins, 256)
+    _check(ref, B, O, reads, es, bins, 256, copies=400)
     _check(ref, B, O, reads, es, bins, 256, copies=2000)
