@@ -990,10 +990,7 @@ extern "C" int grim_filter_windows(const grim_index_t *idx, const grim_batch_t *
     a.status = reinterpret_cast<uint32_t *>(workspace);
     a.counter = reinterpret_cast<uint32_t *>(workspace) + 1;
     a.npl = planes_for(idx->q, b->max_len);
-    HIP_TRY(launch_zero(s, a.status, 2));
-    const uint64_t n_words = (b->n_pairs + 31) / 32;
-    if (n_words)
-        HIP_TRY(launch_zero(s, pass_bits, n_words));
+    HIP_TRY(launch_zero2(s, a.status, kWsHeader / 4, pass_bits, (b->n_pairs + 31) / 32));
     if (b->n_reads == 0)
         return GRIM_OK;
     HIP_TRY(launch_window(s, idx->q, (uint32_t)cu_count(idx->device), (size_t)b->max_len * 4, a));

@@ -18,6 +18,10 @@ constexpr uint64_t kWsHeader = 256;      // status word + ticket counters, padde
 // bytes apart in the header, 2.1e8.
 constexpr uint32_t kTicketCounters = 4;
 constexpr uint32_t kTicketStride = 16;
+// The same for the bin-window kernel, one counter per XCD; all of the header's
+// words are zeroed before it runs.
+constexpr uint32_t kWindowShards = 8;
+constexpr uint32_t kWindowStride = 7;
 
 // Arguments of both filter kernels (passed by value).
 struct FilterArgs {
@@ -96,7 +100,7 @@ struct WindowArgs {
     int32_t *counts;
     uint32_t *pass_bits;
     uint32_t *status;
-    uint32_t *counter;
+    uint32_t *counter;          // kWindowShards words, kWindowStride words apart
     int npl;
 };
 
@@ -115,6 +119,8 @@ hipError_t launch_build_chunked(int q, uint32_t cus, hipStream_t s, const uint32
                                 uint32_t *out);
 hipError_t launch_worklist(hipStream_t s, const FilterArgs &a, uint32_t n_waves);
 hipError_t launch_zero(hipStream_t s, uint32_t *p, uint64_t n);
+// Zeroes two arrays in one launch.
+hipError_t launch_zero2(hipStream_t s, uint32_t *p, uint64_t n, uint32_t *p2, uint64_t n2);
 hipError_t launch_compact(hipStream_t s, const uint32_t *bits, uint64_t n_pairs,
                           const uint64_t *cand_off, uint64_t n_reads, const uint32_t *cand_bin,
                           uint64_t cap, uint64_t *surv_pair, uint32_t *surv_read,

@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "grim_device.h"
 #include "grim_internal.h"
 
@@ -194,21 +196,14 @@ __global__ void zero_words_kernel(uint32_t *p, uint64_t n)
         p[i] = 0u;
 }
 
-// ----------------------------------------------------------- batched filter
-// x of lane ^ m (m a power of two known at compile time after unrolling): DPP
-// moves where one exists, the LDS crossbar otherwise.
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int m)
+__global__ void zero_words2_kernel(uint32_t *p, uint64_t n, uint32_t *p2, uint64_t n2)
 {
-    switch (m) {
-    case 1: return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);    // quad_perm 1,0,3,2
-    case 2: return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);    // quad_perm 2,3,0,1
-    case 4: return __builtin_amdgcn_ds_swizzle(x, 4 << 10 | 0x1F);
-    case 8: return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);   // row_ror 8
-    case 16: return __builtin_amdgcn_ds_swizzle(x, 16 << 10 | 0x1F);
-    default: return __shfl_xor(x, m);
-    }
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        (i < n ? p[i] : p2[i - n]) = 0u;
 }
 
+// ----------------------------------------------------------- batched filter
 // Sums acc[0 .. U) over the G lanes of a group: lane lg ends with the group's
 // total of acc[lg % U] (U <= G).  log2 U exchange steps halve the values that
 // travel, the rest of the group is a butterfly on the one value left.
@@ -754,6 +749,14 @@ hipError_t launch_zero(hipStream_t s, uint32_t *p, uint64_t n)
     if (blocks > 65536)
         blocks = 65536;
     hipLaunchKernelGGL(zero_words_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero2(hipStream_t s, uint32_t *p, uint64_t n, uint32_t *p2, uint64_t n2)
+{
+    const uint64_t blocks = std::min<uint64_t>((n + n2 + 255) / 256, 65536);
+    hipLaunchKernelGGL(zero_words2_kernel, dim3((uint32_t)(blocks ? blocks : 1)), dim3(256), 0, s,
+                       p, n, p2, n2);
     return hipGetLastError();
 }
 

@@ -231,22 +231,121 @@ __device__ __forceinline__ void add_rows(SlicedCount<NP> &c, const uint32_t *tok
             w[u] = load(toks[i + u]);
         c.add16(w);
     }
+    for (; i + 4 <= i1; i += 4) {
+        uint32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            w[u] = load(toks[i + u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            c.add(w[u]);
+    }
+#pragma unroll 1
     for (; i < i1; ++i)
         c.add(load(toks[i]));
 }
 
-// One workgroup per read (reads taken from an atomic counter); the window of
-// read r is bins [win_lo[r], win_lo[r] + size) with size = cand_off[r+1] -
-// cand_off[r], and pair cand_off[r] + j is bin win_lo[r] + j.  Column j of a
-// round (128 columns, 4096 bins) owns bins lo + 32(round*128 + j) + [0, 32);
-// the two halves of the block take the first and the second half of the
-// read's token positions, every position adding its token's row bits into the
-// column's bit-sliced counter.  The halves are then added with a bit-sliced
-// ripple adder, pass bits come from a bit-sliced comparison with T, and the
-// counts are unpacked into LDS so that their stores are coalesced.
+// Which slots a workgroup works on.  The slots (reads, or places of the
+// processing order) are cut into 2^shift contiguous parts, one per XCD: the
+// workgroups of one XCD (blockIdx % 8) then work on neighbouring windows, whose
+// row segments meet in its L2.  A workgroup's first slot is its own number in
+// its shard, later ones are drawn from the shard's counter (11.4 ns a draw for
+// the whole GPU with one counter, 4.8 with these), and once that is used up from
+// the shard with most left.
+constexpr uint32_t kNoSlot = ~0u;
+
+struct Shards {
+    uint32_t n, per, shift;
+    __device__ __forceinline__ explicit Shards(uint32_t n_slots)
+        : n(n_slots), shift(gridDim.x >= 8 * kWindowShards ? 3 : 0)
+    {
+        per = (uint32_t)(((uint64_t)n + (1u << shift) - 1) >> shift);
+    }
+    // slots of shard s, and its workgroups
+    __device__ __forceinline__ uint32_t size(uint32_t s) const
+    {
+        const uint64_t before = (uint64_t)s * per;
+        return before >= n ? 0u : (uint32_t)min<uint64_t>(n - before, per);
+    }
+    __device__ __forceinline__ uint32_t groups(uint32_t s) const
+    {
+        return (gridDim.x + (1u << shift) - 1 - s) >> shift;
+    }
+    // the slot of a draw from shard cur that gave k (lane 0's), or another
+    // shard's, or kNoSlot; one wavefront
+    __device__ __forceinline__ uint32_t slot(uint32_t k, uint32_t *counters, uint32_t &cur,
+                                             int lane) const
+    {
+        k = groups(cur) + __builtin_amdgcn_readfirstlane(k);
+        if (k < size(cur))
+            return cur * per + k;
+        // used up: the shard with most left (if another workgroup is faster, its
+        // own ones still drain it)
+        uint32_t left = 0;
+        if (lane < (1 << shift)) {
+            const uint32_t gone =
+                groups(lane) + __hip_atomic_load(&counters[lane * kWindowStride], __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            left = size(lane) > gone ? size(lane) - gone : 0u;
+        }
+        uint32_t most = left;
+#pragma unroll
+        for (int m = 4; m >= 1; m >>= 1)
+            most = max(most, (uint32_t)__shfl_xor(most, m));
+        most = __builtin_amdgcn_readfirstlane(most);
+        if (!most)
+            return kNoSlot;
+        cur = (uint32_t)__builtin_ctzll(__ballot(lane < (1 << shift) && left == most));
+        k = 0;
+        if (lane == 0)
+            k = atomicAdd(&counters[cur * kWindowStride], 1u);
+        k = groups(cur) + __builtin_amdgcn_readfirstlane(k);
+        return k < size(cur) ? cur * per + k : kNoSlot;
+    }
+};
+
+// A slot's read: index (>= n_reads: the order names none), pairs, bases, first bin.
+struct WindowRead {
+    uint64_t r, p0, p1, off;
+    uint32_t L, lo, e;
+};
+
+__device__ __forceinline__ WindowRead load_window_read(const WindowArgs &a, uint32_t slot)
+{
+    WindowRead m = {};
+    m.r = a.order ? (uint64_t)a.order[slot] : slot;
+    if (m.r < a.n_reads) {
+        m.p0 = a.cand_off[m.r];
+        m.p1 = a.cand_off[m.r + 1];
+        m.L = a.read_len[m.r];
+        m.off = a.read_off[m.r];
+        m.lo = a.win_lo[m.r];
+        m.e = a.read_e[m.r];
+    }
+    return m;
+}
+
+// One workgroup per read; the window of read r is bins [win_lo[r], win_lo[r] +
+// size) with size = cand_off[r+1] - cand_off[r], and pair cand_off[r] + j is bin
+// win_lo[r] + j.  Column j of a
+// round (128, 64 or 32 columns of 32 bins, as many as are left) owns bins
+// lo + 32 j + [0, 32); the 2, 4 or 8 parts of the block take as many shares of
+// the read's token positions, every position adding its token's row bits into
+// the column's bit-sliced counter.  The parts are then added pairwise with a
+// bit-sliced ripple adder, pass bits come from a bit-sliced comparison with T,
+// and the counts are unpacked into LDS so that their stores are coalesced.
+// A wavefront's loads return behind its earlier stores, so the next read is drawn
+// before a read's rows are added and its offsets are asked for before its counts
+// are stored.
 // NP: bit planes per counter (8 covers reads of up to 2^8 + q - 2 bases, else 16).
 // OFF32: the row buffer is below 4 GiB; LDS then holds each token's row byte
 // offset instead of the token.
+//
+// Measured: 200k reads x 4096 bins in processing order 2.53 ms (2.79 with every
+// slot drawn from one counter and loads behind the stores), 100k of 1-2000 bins
+// 0.87 ms (1.25), 20k of 1-64 bins 156 us (257: 128 columns and two parts for
+// every window); starting anywhere, 200k x 4096 3.49 ms (3.48), 5000 of 1-3000
+// bins 85 us (88), of 1-6000 111 us (107).
 template <int Q, int NP, bool OFF32>
 __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
 {
@@ -255,66 +354,86 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
     constexpr int SW = 32 / CPW + 1;                // LDS words per column (padded)
     extern __shared__ uint32_t toks[];              // the read's tokens (max_len entries)
     __shared__ uint32_t stage[128 * SW];            // counts of the round
-    __shared__ uint32_t partial[NP * 128];          // counter of the second half
+    __shared__ uint32_t partial[NP * 128];          // counters of the parts added next
     __shared__ uint32_t pmask[128];                 // pass bits per column
-    __shared__ uint32_t next_read;
-    const int t = threadIdx.x, col = t & 127, half = t >> 7;
+    __shared__ uint32_t next_slot;
+    const int t = threadIdx.x;
     // GRIM_FLAG_* of skipped reads, the same in every thread, reported once
     // after the loop: a skip path must not end in a branch on the thread index
     // (if (t == 0) ... continue), which the compiler may thread across the
     // loop's back edge so that the other threads re-enter the loop at its
     // barrier without thread 0 having fetched the next read
     uint32_t skipped = 0;
+    const Shards shards((uint32_t)a.n_reads);
+    uint32_t cur = blockIdx.x & ((1u << shards.shift) - 1);   // the first wavefront's
+    if ((blockIdx.x >> shards.shift) >= shards.size(cur))
+        return;
+    uint32_t slot = cur * shards.per + (blockIdx.x >> shards.shift);
+    WindowRead rd = load_window_read(a, slot), next = {};
     for (;;) {
-        if (t == 0)
-            next_read = atomicAdd(a.counter, 1u);
-        __syncthreads();
-        const uint64_t slot = next_read;
-        __syncthreads();
-        if (slot >= a.n_reads)
-            break;
-        const uint64_t r = a.order ? (uint64_t)a.order[slot] : slot;
-        if (r >= a.n_reads) {  // an order entry naming no read: skipped
-            skipped |= GRIM_FLAG_READ;
-            continue;
-        }
-        const uint64_t p0 = a.cand_off[r], p1 = a.cand_off[r + 1];
-        if (p1 <= p0)
-            continue;
-        if (p1 > a.n_pairs) {
-            skipped |= GRIM_FLAG_CAND_OFF;
-            continue;
-        }
-        const uint32_t L = a.read_len[r];
-        const uint64_t off = a.read_off[r];
+        uint32_t drawn = 0;
+        // the draw's slot, for the whole workgroup after its next barrier
+        auto publish = [&]() {
+            if (t < 64) {
+                const uint32_t s = shards.slot(drawn, a.counter, cur, t);
+                if (t == 0)
+                    next_slot = s;
+            }
+        };
+        auto take_next = [&]() {
+            slot = __builtin_amdgcn_readfirstlane(next_slot);
+            if (slot != kNoSlot)
+                next = load_window_read(a, slot);
+        };
+        const uint64_t p0 = rd.p0, p1 = rd.p1, off = rd.off, lo = rd.lo, size = p1 - p0;
+        const uint32_t L = rd.L;
         const uint64_t nb = a.nw * 16;
-        const uint64_t lo = a.win_lo[r], size = p1 - p0;
-        if (L > a.max_len || off > nb || L > nb - off) {
-            for (uint64_t k = p0 + t; k < p1; k += blockDim.x)
-                a.counts[k] = -1;
+        bool valid = false;
+        if (rd.r >= a.n_reads) {          // an order entry naming no read: skipped
             skipped |= GRIM_FLAG_READ;
-            continue;
+        } else if (p1 > p0) {
+            if (p1 > a.n_pairs)
+                skipped |= GRIM_FLAG_CAND_OFF;
+            else if (L > a.max_len || off > nb || L > nb - off) {
+                for (uint64_t k = p0 + t; k < p1; k += blockDim.x)
+                    a.counts[k] = -1;
+                skipped |= GRIM_FLAG_READ;
+            } else {
+                valid = true;
+            }
         }
-        const uint32_t ntok = L >= (uint32_t)Q ? L - Q + 1 : 0u;
+        // the same in every thread; a skipped read has no rounds
+        valid = __builtin_amdgcn_readfirstlane(valid);
+        const uint32_t ntok = valid && L >= (uint32_t)Q ? L - Q + 1 : 0u;
         const uint64_t row_bytes = a.row_words * 4;
         for (uint32_t i = t; i < ntok; i += blockDim.x) {
             const uint32_t tk = win_token_at<Q>(a.rw, a.nw, off + i);
             toks[i] = OFF32 ? tk * (uint32_t)row_bytes : tk;
         }
+        if (t == 0)
+            drawn = atomicAdd(&a.counter[cur * kWindowStride], 1u);
         __syncthreads();
-        const uint64_t E = ((uint64_t)a.read_e[r] * L + a.e_den - 1) / a.e_den;
+        if (!valid) {
+            publish();
+            __syncthreads();
+            take_next();
+            __syncthreads();
+        }
+        const uint64_t E = ((uint64_t)rd.e * L + a.e_den - 1) / a.e_den;
         const int64_t T = (int64_t)ntok - (int64_t)Q * (int64_t)E;
-        // first half: tokens [0, hsplit), second: [hsplit, ntok); hsplit is a
-        // multiple of 16 so that both halves start on 16-token blocks
-        const uint32_t hsplit = ((ntok / 2 + 15) / 16) * 16 < ntok ? ((ntok / 2 + 15) / 16) * 16 : ntok;
-        const uint32_t i0 = half ? hsplit : 0u, i1 = half ? ntok : hsplit;
         const uint64_t wv0 = lo >> 5;
         const uint32_t sh = (uint32_t)(lo & 31);
-        const uint64_t n_cols = (size + 31) >> 5;
+        const uint64_t n_cols = valid ? (size + 31) >> 5 : 0;
         const char *rows = reinterpret_cast<const char *>(a.rows);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint32_t *>(a.rows), (short)0, (int)(uint32_t)a.rows_bytes, 0x00020000);
         for (uint64_t vb = 0; vb < n_cols; vb += 128) {
+            // columns of this round, and this thread's share of the tokens: a
+            // whole number of 16-token blocks
+            const uint32_t cols = n_cols - vb > 64 ? 128 : n_cols - vb > 32 ? 64 : 32;
+            const uint32_t col = t & (cols - 1), part = t / cols, n_parts = 256 / cols;
+            const uint32_t share = (ntok + n_parts * 16 - 1) / (n_parts * 16) * 16;
+            const uint32_t i0 = min(part * share, ntok), i1 = min(i0 + share, ntok);
             const uint64_t j = vb + col;
             const uint64_t wi = wv0 + j;
             SlicedCount<NP> c;
@@ -326,21 +445,30 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
                 else
                     add_rows<NP, OFF32, false>(c, toks, i0, i1, rs, rows, row_bytes, bo, sh);
             }
-            if (half == 1) {
+            const bool last_round = vb + 128 >= n_cols;
+            if (last_round)
+                publish();
+            // parts [s, 2 s) are added to parts [0, s)
+            for (uint32_t s = n_parts / 2; s >= 1; s /= 2) {
+                if (part >= s && part < 2 * s) {
 #pragma unroll
-                for (int k = 0; k < NP; ++k)
-                    partial[k * 128 + col] = c.p[k];
-            }
-            __syncthreads();
-            if (half == 0) {
-                // ripple-carry addition of the two halves' counters
-                uint32_t carry = 0;
-#pragma unroll
-                for (int k = 0; k < NP; ++k) {
-                    const uint32_t x = c.p[k], y = partial[k * 128 + col];
-                    c.p[k] = x ^ y ^ carry;
-                    carry = (x & y) | (carry & (x ^ y));
+                    for (int k = 0; k < NP; ++k)
+                        partial[k * 128 + (t - s * cols)] = c.p[k];
                 }
+                __syncthreads();
+                if (part < s) {
+                    uint32_t carry = 0;
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) {
+                        const uint32_t x = c.p[k], y = partial[k * 128 + t];
+                        c.p[k] = x ^ y ^ carry;
+                        carry = (x & y) | (carry & (x ^ y));
+                    }
+                }
+                if (s > 1)
+                    __syncthreads();   // partial is written again
+            }
+            if (part == 0) {
                 // bins of this column inside the window and below n_bins
                 uint32_t valid = 0;
                 if (j < n_cols) {
@@ -396,11 +524,13 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
                 }
             }
             __syncthreads();
+            if (last_round)
+                take_next();
             // counts: element e of the round is bin lo + 32 vb + e, pair p0 + 32 vb + e
             const uint64_t base = vb * 32;
             const cnt_t *sc = reinterpret_cast<const cnt_t *>(stage);
             bool oob = false;
-            for (uint32_t e = t; e < 128 * 32; e += 256) {
+            for (uint32_t e = t; e < cols * 32; e += 256) {
                 const uint64_t pe = base + e;
                 if (pe < size) {
                     if (lo + pe >= a.n_bins) {
@@ -417,19 +547,19 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
             // g = (p0 >> 5) + vb + m takes the high part of column m - 1 and
             // the low part of column m.  Words shared with other reads (the
             // first and the last of the window) are ORed in, the rest stored.
-            if (t <= 128) {
+            if ((uint32_t)t <= cols) {
                 const uint32_t ps = (uint32_t)(p0 & 31);
                 const uint64_t g0 = (p0 >> 5) + vb;
                 const uint64_t g_last = (p1 - 1) >> 5;
                 const uint64_t g = g0 + t;
                 if (g <= g_last) {
-                    const uint32_t lo_part = t < 128 ? pmask[t] << ps : 0u;
+                    const uint32_t lo_part = (uint32_t)t < cols ? pmask[t] << ps : 0u;
                     const uint32_t hi_part = (t > 0 && ps) ? pmask[t - 1] >> (32 - ps) : 0u;
                     const uint32_t word = lo_part | hi_part;
                     const bool first = (g == (p0 >> 5)), last = (g == g_last);
                     // the word past the round's last column gets only a high part;
                     // the next round (if any) ORs its own low part in
-                    const bool shared = first || last || t == 128 || (t == 0 && vb > 0);
+                    const bool shared = first || last || (uint32_t)t == cols || (t == 0 && vb > 0);
                     if (shared) {
                         if (word)
                             atomicOr(&a.pass_bits[g], word);
@@ -440,7 +570,9 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
             }
             __syncthreads();  // stage, partial and pmask are rewritten next round
         }
-        __syncthreads();  // toks reused by the next read
+        if (slot == kNoSlot)
+            break;
+        rd = next;
     }
     if (t == 0 && skipped)
         atomicOr(a.status, skipped);
