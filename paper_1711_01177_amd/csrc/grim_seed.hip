@@ -24,6 +24,7 @@
 #include <utility>
 #include <vector>
 
+#include "grim_device.h"
 #include "grim_internal.h"
 
 // Result buffers of freed candidate lists, kept for the next lists of the same
@@ -464,6 +465,22 @@ __device__ __forceinline__ void sort_keys(Arr x, uint64_t m, int lane, Fence fen
     }
 }
 
+// One comparator of every lane with lane ^ m, whose top bit is j: the lane with
+// that bit set keeps the larger key.
+__device__ __forceinline__ uint32_t compare_lanes(uint32_t v, int m, int j, int lane)
+{
+    if (m == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return lane & 16 ? max(r[0], r[1]) : min(r[0], r[1]);
+    }
+    if (m == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return lane & 32 ? max(r[0], r[1]) : min(r[0], r[1]);
+    }
+    const uint32_t w = lane_xor(v, m);
+    return lane & j ? max(v, w) : min(v, w);
+}
+
 // The same network on one key per lane (m <= 64 keys; lanes >= m hold +inf),
 // with the partners exchanged by cross-lane moves; only the stages up to the
 // power of two P >= m run (each block of P lanes is sorted on its own, and the
@@ -476,9 +493,7 @@ __device__ __forceinline__ uint32_t sort_lanes(uint32_t v, int lane, uint32_t m)
             break;
 #pragma unroll
         for (int j = k >> 1; j >= 1; j >>= 1) {
-            const int partner = j == (k >> 1) ? (lane ^ (k - 1)) : (lane ^ j);
-            const uint32_t w = __shfl(v, partner);
-            v = lane < partner ? min(v, w) : max(v, w);
+            v = compare_lanes(v, j == (k >> 1) ? k - 1 : j, j, lane);
         }
     }
     return v;
@@ -514,10 +529,19 @@ __device__ __forceinline__ uint64_t unique_keys(Src x, uint64_t m, uint32_t cap,
 // apart exchange registers of one lane, the others exchange one register
 // between lanes; the first step of a stage above 64 does both (key e pairs
 // with e ^ (k - 1): lane ^ 63 in register r ^ ((k - 1) >> 6)).
+//
+// Exchanges between lanes are DPP moves and row swaps up to kDppKeys keys a lane
+// and go through the LDS crossbar above that: the moves take more instructions,
+// and the larger networks, all unrolled, leave the instruction cache with them
+// (20k reads of 513-2048 keys: 1.49 ms, 0.21 through the crossbar; 1M reads of up
+// to 512: 392 us at 4, 417 at 8, 527 with the crossbar throughout).
+constexpr int kDppKeys = 4;
+
 template <int R>
 __device__ __forceinline__ void sort_regs(uint32_t (&v)[R], int lane)
 {
     constexpr int P = kWave * R;
+    constexpr bool kCrossbar = R > kDppKeys;
 #pragma unroll
     for (int k = 2; k <= P; k <<= 1) {
 #pragma unroll
@@ -529,8 +553,10 @@ __device__ __forceinline__ void sort_regs(uint32_t (&v)[R], int lane)
                 for (int r = 0; r < R; ++r) {
                     const int r2 = r ^ rm;
                     if (r < r2) {
-                        const uint32_t t1 = __shfl(v[r2], lane ^ (kWave - 1));
-                        const uint32_t t2 = __shfl(v[r], lane ^ (kWave - 1));
+                        const uint32_t t1 = kCrossbar ? __shfl(v[r2], lane ^ (kWave - 1))
+                                                      : lane_xor(v[r2], kWave - 1);
+                        const uint32_t t2 = kCrossbar ? __shfl(v[r], lane ^ (kWave - 1))
+                                                      : lane_xor(v[r], kWave - 1);
                         v[r] = min(v[r], t1);
                         v[r2] = max(v[r2], t2);
                     }
@@ -547,11 +573,15 @@ __device__ __forceinline__ void sort_regs(uint32_t (&v)[R], int lane)
                     }
                 }
             } else {
-                const int partner = flip ? (lane ^ (k - 1)) : (lane ^ j);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const uint32_t w = __shfl(v[r], partner);
-                    v[r] = lane < partner ? min(v[r], w) : max(v[r], w);
+                    if (kCrossbar) {
+                        const int partner = flip ? (lane ^ (k - 1)) : (lane ^ j);
+                        const uint32_t w = __shfl(v[r], partner);
+                        v[r] = lane < partner ? min(v[r], w) : max(v[r], w);
+                    } else {
+                        v[r] = compare_lanes(v[r], flip ? k - 1 : j, j, lane);
+                    }
                 }
             }
         }
