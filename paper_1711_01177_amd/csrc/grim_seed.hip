@@ -55,6 +55,22 @@ struct SeedBufferCache {
         bufs.erase(bufs.begin() + best);
         return b;
     }
+    // the largest cached buffer of at least `bytes` bytes, or null
+    uint8_t *take_largest(uint64_t bytes, uint64_t *got)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        size_t best = bufs.size();
+        for (size_t i = 0; i < bufs.size(); ++i)
+            if (bufs[i].second >= bytes &&
+                (best == bufs.size() || bufs[i].second > bufs[best].second))
+                best = i;
+        if (best == bufs.size())
+            return nullptr;
+        uint8_t *b = bufs[best].first;
+        *got = bufs[best].second;
+        bufs.erase(bufs.begin() + best);
+        return b;
+    }
     // keep a buffer no queued work uses any more; the smallest one goes when
     // more than kCachedBuffers are held
     void give(uint8_t *b, uint64_t bytes)
@@ -97,6 +113,8 @@ struct grim_seed_index {
     std::mutex mu;
     uint8_t *tmp[3] = {nullptr, nullptr, nullptr};
     uint64_t tmp_bytes[3] = {0, 0, 0};
+    // page-locked words the kernels report a call's hits and pairs in
+    uint64_t *h_totals = nullptr;
     std::shared_ptr<SeedBufferCache> cache;
 };
 
@@ -194,7 +212,9 @@ __global__ __launch_bounds__(256) void scan_totals_kernel(const T *__restrict__ 
         block_tot[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void scan_tot_kernel(uint64_t *sums, uint64_t n, uint64_t *total)
+// host, host_of (may be null): page-locked words that get the total and *extra.
+__global__ __launch_bounds__(1024) void scan_tot_kernel(uint64_t *sums, uint64_t n, uint64_t *total,
+                                                        uint64_t *host, const uint64_t *extra)
 {
     __shared__ uint64_t part[16];
     __shared__ uint64_t carry_s;
@@ -228,8 +248,13 @@ __global__ __launch_bounds__(1024) void scan_tot_kernel(uint64_t *sums, uint64_t
             carry_s += all;
         __syncthreads();
     }
-    if (t == 0)
+    if (t == 0) {
         *total = carry_s;
+        if (host) {
+            host[0] = carry_s;
+            host[1] = extra ? *extra : carry_s;
+        }
+    }
 }
 
 // The block's kScanPerBlock inputs go through LDS: loaded and stored with
@@ -372,8 +397,11 @@ __global__ __launch_bounds__(256) void seed_hit_off_kernel(const uint64_t *__res
 __global__ __launch_bounds__(256) void seed_emit_kernel(
     const uint32_t *__restrict__ item_a, const uint32_t *__restrict__ item_o,
     const uint64_t *__restrict__ item_off, uint64_t n_items,
-    const uint32_t *__restrict__ idx_pos, uint64_t G, uint64_t B, uint32_t *__restrict__ hb)
+    const uint32_t *__restrict__ idx_pos, uint64_t G, uint64_t B, uint64_t hits_cap,
+    uint32_t *__restrict__ hb)
 {
+    if (item_off[n_items] > hits_cap)
+        return;
     const int lane = threadIdx.x & 63;
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
     for (uint64_t i0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * kWave;
@@ -646,10 +674,12 @@ constexpr int kSortWaves = 4;
 constexpr int kSortReads = 4;  // consecutive reads per wavefront, their loads in flight together
 
 __global__ __launch_bounds__(kSortWaves * kWave) void seed_sort_kernel(
-    const uint64_t *__restrict__ hit_off, uint64_t n_reads, uint32_t cap, uint32_t *__restrict__ hb,
-    uint64_t *__restrict__ ucnt, uint32_t *__restrict__ long_list,
+    const uint64_t *__restrict__ hit_off, uint64_t n_reads, uint64_t hits_cap, uint32_t cap,
+    uint32_t *__restrict__ hb, uint64_t *__restrict__ ucnt, uint32_t *__restrict__ long_list,
     uint32_t *__restrict__ long_count)
 {
+    if (hit_off[n_reads] > hits_cap)   // nothing joins the long list either
+        return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t r0 = ((uint64_t)blockIdx.x * kSortWaves + wv) * kSortReads;
     if (r0 >= n_reads)
@@ -765,9 +795,11 @@ constexpr int kCopyBatch = 8;
 __global__ __launch_bounds__(256) void seed_compact_kernel(const uint32_t *__restrict__ list,
                                                            const uint64_t *__restrict__ hit_off,
                                                            const uint64_t *__restrict__ cand_off,
-                                                           uint64_t n_reads,
+                                                           uint64_t n_reads, uint64_t hits_cap,
                                                            uint32_t *__restrict__ out)
 {
+    if (hit_off[n_reads] > hits_cap)
+        return;
     // the group's next read's offsets load while this one is copied, and each
     // lane loads kCopyBatch values before it stores any, so that a read of up
     // to kCopyGroup * kCopyBatch bins costs one round trip
@@ -810,7 +842,8 @@ __global__ __launch_bounds__(256) void seed_compact_kernel(const uint32_t *__res
 }
 
 hipError_t scan_u64(hipStream_t s, const void *in, bool in_u32, uint64_t n, uint64_t *out,
-                    uint64_t *block_tmp, uint64_t *total_tmp)
+                    uint64_t *block_tmp, uint64_t *total_tmp, uint64_t *host = nullptr,
+                    const uint64_t *extra = nullptr)
 {
     const uint64_t nb = (n + kScanPerBlock - 1) / kScanPerBlock;
     const uint64_t blocks = nb ? nb : 1;
@@ -820,7 +853,8 @@ hipError_t scan_u64(hipStream_t s, const void *in, bool in_u32, uint64_t n, uint
     else
         hipLaunchKernelGGL(scan_totals_kernel<uint64_t>, dim3((uint32_t)blocks), dim3(256), 0, s,
                            static_cast<const uint64_t *>(in), n, block_tmp);
-    hipLaunchKernelGGL(scan_tot_kernel, dim3(1), dim3(1024), 0, s, block_tmp, blocks, total_tmp);
+    hipLaunchKernelGGL(scan_tot_kernel, dim3(1), dim3(1024), 0, s, block_tmp, blocks, total_tmp, host,
+                       extra);
     if (in_u32)
         hipLaunchKernelGGL(scan_apply_kernel<uint32_t>, dim3((uint32_t)blocks), dim3(256), 0, s,
                            static_cast<const uint32_t *>(in), n, block_tmp, total_tmp, out);
@@ -893,7 +927,9 @@ extern "C" int grim_seed_index_build(const uint32_t *ref_2bit, uint64_t ref_len,
     if (hipMalloc(&d_ref, nw * 4) != hipSuccess || hipMalloc(&cnt, nk * 4) != hipSuccess ||
         hipMalloc(&btmp, (scan_blocks(nk) + 1) * 8) != hipSuccess ||
         hipMalloc(&si->d_off, (nk + 1) * 8) != hipSuccess ||
-        hipMalloc(&si->d_pos, npos * 4) != hipSuccess) {
+        hipMalloc(&si->d_pos, npos * 4) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&si->h_totals), 64, hipHostMallocDefault) !=
+            hipSuccess) {
         rc = GRIM_E_NOMEM;
         goto done;
     }
@@ -915,6 +951,8 @@ done:
     if (rc != GRIM_OK) {
         (void)hipFree(si->d_off);
         (void)hipFree(si->d_pos);
+        if (si->h_totals)
+            (void)hipHostFree(si->h_totals);
         delete si;
         return rc;
     }
@@ -930,6 +968,7 @@ extern "C" void grim_seed_index_free(grim_seed_index_t *si)
     (void)hipFree(si->d_pos);
     for (uint8_t *t : si->tmp)
         (void)hipFree(t);
+    (void)hipHostFree(si->h_totals);
     delete si;
 }
 
@@ -1051,64 +1090,91 @@ extern "C" int grim_seed_candidates(const grim_seed_index_t *csi, const grim_bat
                            si->k, si->d_off, item_a, item_cnt, item_o);
         SEED_TRY(hipGetLastError());
     }
-    SEED_TRY(scan_u64(s, item_cnt, true, n_items, item_off, itmp,
-                      itmp + scan_blocks(n_items)));
+    SEED_TRY(scan_u64(s, item_cnt, true, n_items, item_off, itmp, itmp + scan_blocks(n_items),
+                      si->h_totals));
     hipLaunchKernelGGL(seed_hit_off_kernel, dim3(grid_for(n + 1, dev)), dim3(256), 0, s,
                        fixed ? nullptr : item_base, (uint64_t)S, item_off, n, hit_off, long_count);
     SEED_TRY(hipGetLastError());
-    SEED_TRY(hipMemcpyAsync(&total_hits, item_off + n_items, 8, hipMemcpyDeviceToHost, s));
-    SEED_TRY(hipStreamSynchronize(s));
-    if (total_hits >= 0x7fffffffull) {
-        rc = GRIM_E_UNSUPPORTED;
-        goto done;
-    }
-    // every hit's bin, then the per-read lists in place; the result (offsets
-    // and bins in one allocation) is no longer than the hits together
-    hb = reinterpret_cast<uint32_t *>(seed_tmp(si, 2, (total_hits + 1) * 4));
+    // Every hit's bin, then the per-read lists in place; the result (offsets and
+    // bins in one allocation) is no longer than the hits together.  A call that
+    // finds buffers of earlier calls queues all of it for as many hits as those
+    // hold, without waiting for the number (the wait cost 24 us of the chain of 5000
+    // reads, 42 of a million reads); the kernels do nothing when there are more, and
+    // the second round allocates for the number that is known then.
     {
-        const uint64_t need = align_up((n + 1) * 8, 256) + (total_hits + 1) * 4;
-        c->buf = si->cache->take(need, &c->buf_bytes);
-        if (!c->buf) {
-            c->buf_bytes = align_up(need, 2ull << 20);
-            if (hipMalloc(&c->buf, c->buf_bytes) != hipSuccess)
-                c->buf = nullptr;
+        const uint64_t offs = align_up((n + 1) * 8, 256);
+        uint64_t hits_cap = 0;
+        if (si->tmp_bytes[2] >= 8)
+            c->buf = si->cache->take_largest(offs + 8, &c->buf_bytes);
+        if (c->buf) {
+            c->cache = si->cache;
+            hits_cap = std::min<uint64_t>({si->tmp_bytes[2] / 4 - 1, (c->buf_bytes - offs) / 4 - 1,
+                                           0x7ffffffeull});
+        }
+        bool known = !c->buf;
+        for (;;) {
+            if (known) {
+                SEED_TRY(hipStreamSynchronize(s));
+                total_hits = si->h_totals[1];
+                if (total_hits >= 0x7fffffffull) {
+                    rc = GRIM_E_UNSUPPORTED;
+                    goto done;
+                }
+                hits_cap = total_hits;
+                const uint64_t need = offs + (total_hits + 1) * 4;
+                c->buf = si->cache->take(need, &c->buf_bytes);
+                if (!c->buf) {
+                    c->buf_bytes = align_up(need, 2ull << 20);
+                    if (hipMalloc(&c->buf, c->buf_bytes) != hipSuccess)
+                        c->buf = nullptr;
+                }
+                c->cache = si->cache;
+                if (!c->buf || !seed_tmp(si, 2, (total_hits + 1) * 4)) {
+                    rc = GRIM_E_NOMEM;
+                    goto done;
+                }
+            }
+            hb = reinterpret_cast<uint32_t *>(si->tmp[2]);
+            c->d_off = reinterpret_cast<uint64_t *>(c->buf);
+            c->d_bin = reinterpret_cast<uint32_t *>(c->buf + offs);
+            if (n) {
+                if (n_items) {
+                    hipLaunchKernelGGL(seed_emit_kernel, dim3(grid_for(n_items, dev)), dim3(256), 0,
+                                       s, item_a, item_o, item_off, n_items, si->d_pos, si->G,
+                                       bin_stride, hits_cap, hb);
+                    SEED_TRY(hipGetLastError());
+                }
+                const uint64_t per_block = (uint64_t)kSortWaves * kSortReads;
+                hipLaunchKernelGGL(seed_sort_kernel,
+                                   dim3((uint32_t)((n + per_block - 1) / per_block)),
+                                   dim3(kSortWaves * kWave), 0, s, hit_off, n, hits_cap, cap, hb,
+                                   ucnt, long_list, long_count);
+                SEED_TRY(hipGetLastError());
+                hipLaunchKernelGGL(seed_sort_wide_kernel,
+                                   dim3(grid_for((uint64_t)256 * 8 * 256, dev)), dim3(256), 0, s,
+                                   hit_off, cap, hb, ucnt, long_list, long_count);
+                SEED_TRY(hipGetLastError());
+                hipLaunchKernelGGL(seed_sort_long_kernel,
+                                   dim3(grid_for((uint64_t)256 * 8 * 256, dev)), dim3(256), 0, s,
+                                   hit_off, cap, hb, ucnt, long_list, long_count);
+                SEED_TRY(hipGetLastError());
+            }
+            SEED_TRY(scan_u64(s, ucnt, false, n, c->d_off, btmp, btmp + nbt - 1, si->h_totals,
+                              item_off + n_items));
+            if (n) {
+                hipLaunchKernelGGL(seed_compact_kernel, dim3(grid_for(n * kCopyGroup, dev)),
+                                   dim3(256), 0, s, hb, hit_off, c->d_off, n, hits_cap, c->d_bin);
+                SEED_TRY(hipGetLastError());
+            }
+            SEED_TRY(hipStreamSynchronize(s));
+            n_pairs = si->h_totals[0];
+            if (known || si->h_totals[1] <= hits_cap)
+                break;
+            si->cache->give(c->buf, c->buf_bytes);   // too small, and idle: the stream was waited for
+            c->buf = nullptr;
+            known = true;
         }
     }
-    if (!hb || !c->buf) {
-        rc = GRIM_E_NOMEM;
-        goto done;
-    }
-    c->cache = si->cache;
-    c->d_off = reinterpret_cast<uint64_t *>(c->buf);
-    c->d_bin = reinterpret_cast<uint32_t *>(c->buf + align_up((n + 1) * 8, 256));
-    if (n) {
-        if (n_items) {
-            hipLaunchKernelGGL(seed_emit_kernel, dim3(grid_for(n_items, dev)), dim3(256), 0, s,
-                               item_a, item_o, item_off, n_items, si->d_pos, si->G, bin_stride, hb);
-            SEED_TRY(hipGetLastError());
-        }
-        const uint64_t per_block = (uint64_t)kSortWaves * kSortReads;
-        hipLaunchKernelGGL(seed_sort_kernel, dim3((uint32_t)((n + per_block - 1) / per_block)),
-                           dim3(kSortWaves * kWave), 0, s, hit_off, n, cap, hb, ucnt, long_list,
-                           long_count);
-        SEED_TRY(hipGetLastError());
-    }
-    if (n) {
-        hipLaunchKernelGGL(seed_sort_wide_kernel, dim3(grid_for((uint64_t)256 * 8 * 256, dev)),
-                           dim3(256), 0, s, hit_off, cap, hb, ucnt, long_list, long_count);
-        SEED_TRY(hipGetLastError());
-        hipLaunchKernelGGL(seed_sort_long_kernel, dim3(grid_for((uint64_t)256 * 8 * 256, dev)),
-                           dim3(256), 0, s, hit_off, cap, hb, ucnt, long_list, long_count);
-        SEED_TRY(hipGetLastError());
-    }
-    SEED_TRY(scan_u64(s, ucnt, false, n, c->d_off, btmp, btmp + nbt - 1));
-    if (n) {
-        hipLaunchKernelGGL(seed_compact_kernel, dim3(grid_for(n * kCopyGroup, dev)), dim3(256), 0,
-                           s, hb, hit_off, c->d_off, n, c->d_bin);
-        SEED_TRY(hipGetLastError());
-    }
-    SEED_TRY(hipMemcpyAsync(&n_pairs, c->d_off + n, 8, hipMemcpyDeviceToHost, s));
-    SEED_TRY(hipStreamSynchronize(s));
     c->n_pairs = n_pairs;
 done:
     if (rc != GRIM_OK) {
