@@ -48,3 +48,28 @@ def test_growing_and_shrinking_batches(keep):
         del c
     for c, want in held:
         assert np.array_equal(c.to_host()[1], want)
+
+
+@pytest.mark.parametrize("B", [1, 3, 64, 200, 8191, 1 << 20, (1 << 31) + 1, (1 << 32) - 1, 1 << 32,
+                               1 << 40])
+def test_strides_and_long_groups(B):
+    """Strides around what the multiplied division takes, on reads whose seeds hit
+    once, not at all and thousands of times (groups of 64 items with hits beyond
+    one round of 2048 places)."""
+    g = lib()
+    rng = np.random.default_rng(12)
+    ref = rng.integers(0, 4, 40_000).astype(np.uint8)
+    ref[1000:4100] = 2                          # one k-mer, about 3100 places
+    ref[9000:9600] = np.tile([0, 1], 300)
+    si = g.SeedIndex(ref, 9)
+    batch, codes, off, ln = _batch(g, ref, 300, 95, 5)
+    pick = [(1200, 0), (1200, 50), (9100, 0), (39_905, 0), (0, 0)]
+    for r, (at, flip) in enumerate(pick):
+        codes[r * 95:(r + 1) * 95] = ref[at:at + 95]
+        codes[r * 95 + flip] ^= 1
+    batch = g.Batch(codes, off, ln, np.zeros(300, np.uint32), 10000, np.zeros(301, np.uint64),
+                    np.zeros(0, np.uint32), max_len=95)
+    c = g.grim_seed_candidates(si, batch, B)
+    want_off, want_bin = oracle.seed_candidates(ref, 9, codes, off, ln, B, 4096)
+    got_off, got_bin = c.to_host()
+    assert np.array_equal(got_off, want_off) and np.array_equal(got_bin, want_bin)
