@@ -506,7 +506,9 @@ constexpr uint32_t kOrXor = (0xF0u | (0xCCu ^ 0xAAu)) & 0xFFu;   // a | (b ^ c)
 // Phase A for one wave.  piece: this thread's pieces in LDS (256 threads apart,
 // first base in the top bits); np, m: their number and length (np = 0: lane
 // idle); p: the span's first reference word pair, sh its first base's bit;
-// np_max, span_max: the wave's largest.  [lo, hi] holds the diagonals (span
+// np_max: the wave's largest; span_max: the longest span, which a lane at the
+// reference's end does not reach: p_last is the last word pair it may read.
+// [lo, hi] holds the diagonals (span
 // position minus read position) of every hit; lo > hi without one.
 //
 // Cost: the span's 160 positions are held as bit planes of the two code bits,
@@ -516,8 +518,8 @@ constexpr uint32_t kOrXor = (0xF0u | (0xCCu ^ 0xAAu)) & 0xFFu;   // a | (b ^ c)
 // instructions per piece and 160 positions.
 __device__ __forceinline__ void find_pieces(const uint32_t *piece, uint32_t np, uint32_t m,
                                             uint32_t np_max, bool nine, const uint2 *p,
-                                            uint32_t sh, int32_t span, int32_t span_max,
-                                            int32_t &lo, int32_t &hi)
+                                            uint32_t p_last, uint32_t sh, int32_t span,
+                                            int32_t span_max, int32_t &lo, int32_t &hi)
 {
     constexpr int K = kPieceBases;
     lo = 0x3fffffff;
@@ -529,7 +531,7 @@ __device__ __forceinline__ void find_pieces(const uint32_t *piece, uint32_t np, 
             uint2 w[kGroup + 2];
 #pragma unroll
             for (int i = 0; i < kGroup + 2; ++i)
-                w[i] = p[(at >> 5) + i];
+                w[i] = p[min((uint32_t)(at >> 5) + i, p_last)];
 #pragma unroll
             for (int i = 0; i <= kGroup; ++i) {
                 th[i] = __builtin_amdgcn_alignbit(w[i + 1].x, w[i].x, sh);
@@ -706,13 +708,14 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
 // sorts them (counting sort in LDS): those whose pieces are looked for by their
 // tolerated edits, as many pieces as that takes, then the others by the number
 // of 32-row words of their read, empty slots of a short last chunk last.  Phase
-// A runs over the first part, 256 sorted slots at a time; phase B over the list
-// of bands it leaves (narrow ones from the front, wide ones from the back, so
-// that a wavefront has one kind), phase C over the second part and the few
-// survivors A could not settle.  A survivor's smallest distance is collected in
-// LDS as twice the distance, or 2 E + 1 while none within E is known; distances
-// and pass bits leave together.  W is the number of 64-row blocks (NW = 2 W
-// words) the batch's longest read needs.
+// A runs over the first part, 64 sorted slots a wavefront, drawn from LDS with the
+// most pieces first; phase B over the bands it leaves (narrow ones listed from
+// the front, wide ones from the back, broad ones apart, so that a wavefront has
+// one kind), the longest first; phase C over the second part and the few
+// survivors whose bands found no room.  A survivor's smallest distance is
+// collected in LDS as twice the distance, or 2 E + 1 while none within E is
+// known; distances and pass bits leave together.  W is the number of 64-row
+// blocks (NW = 2 W words) the batch's longest read needs.
 constexpr int kVerifyChunk = 1024;
 constexpr int kVerifySmall = 256;
 
@@ -865,8 +868,10 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
             const uint64_t lo = (uint64_t)b * a.B;
             const int32_t span = (int32_t)span_of(lo);
             int32_t h0, h1;
-            find_pieces(pieces + t, np, m, np_max, nine, a.planes + (lo >> 5), (uint32_t)lo & 31u,
-                        span, (int32_t)span_all, h0, h1);
+            const uint64_t p_left = (a.ref_words + 1) / 2 + kPlanePad - 1 - (lo >> 5);
+            find_pieces(pieces + t, np, m, np_max, nine, a.planes + (lo >> 5),
+                        (uint32_t)min<uint64_t>(p_left, ~0u), (uint32_t)lo & 31u, span,
+                        (int32_t)span_all, h0, h1);
             if (on && h0 <= h1)
                 settle(slot, E, h0, h1);
         }

@@ -54,10 +54,9 @@ struct FilterArgs {
 // Zero words kept after the packed reference for the alignment check, whose
 // look-ahead fetches of reference words run up to three words past the end.
 constexpr uint64_t kRefPadWords = 4;
-// Zero word pairs before and after the reference's bit planes: a band of 64
-// diagonals starts up to a read (512 bases) and its edits before its span and
-// ends as far past it, and the piece search fetches up to 12 pairs past a
-// span's first one.
+// Zero word pairs before and after the reference's bit planes: a band of up to
+// 128 diagonals starts up to a read (512 bases) and its edits before its span and
+// ends as far past it.  The piece search stays within them by itself.
 constexpr uint64_t kPlanePad = 64;
 
 // Arguments of the alignment-check kernel.
