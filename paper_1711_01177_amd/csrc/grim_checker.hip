@@ -480,7 +480,7 @@ __device__ __forceinline__ int32_t column_scan_from(int s, const uint64_t *peq_t
 //
 // The vector ALUs bound it: 2.5M survivors of 100-250 bases at 5-10 % edits take
 // 3.9e8 wavefront instructions (1.06e9 with the scan of all columns for each)
-// and 0.75 ms (1.64), 0.49 of it phase A; 7.4e4 survivors 0.12 ms (0.41).
+// and 0.76 ms (1.64), 0.49 of it phase A; 7.4e4 survivors 0.12 ms (0.41).
 constexpr int kPieces = 32;          // pieces at most (E <= 31: two bands of E fit 64 diagonals)
 constexpr int kPieceMin = 8;         // bases of a piece at least
 constexpr int kPieceBases = 9;       // bases looked for (8 where a lane's pieces have no more)
