@@ -175,26 +175,22 @@ struct SlicedCount {
     }
 };
 
-// Bins lo + 32j + i (i = 0..31) of token row `row` for virtual column j: the
-// row words holding them, joined by a funnel shift.  The row buffer carries one
-// pad word past its last row, so the second word is always readable; bits taken
-// from beyond a row's end belong to bins >= n_bins, which the caller masks.
+// Two adjacent words of token row `row` from byte_off on.  The row buffer carries
+// one pad word past its last row, so the second word is always readable.
 typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t row_bins(const char *__restrict__ row, uint32_t byte_off,
-                                            uint32_t sh)
+__device__ __forceinline__ u32x2 row_pair(const char *__restrict__ row, uint32_t byte_off)
 {
-    const u32x2_a4 v = *reinterpret_cast<const u32x2_a4 *>(row + byte_off);
-    return __builtin_amdgcn_alignbit(v.y, v.x, sh);
+    return *reinterpret_cast<const u32x2_a4 *>(row + byte_off);
 }
 
 // The same through a buffer resource over the whole row buffer, when its size
 // fits 32-bit byte offsets: the row's offset comes from LDS and costs one add.
-__device__ __forceinline__ uint32_t row_bins(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off,
-                                            uint32_t sh)
+__device__ __forceinline__ u32x2 row_pair(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off)
 {
     const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, byte_off, 0, 0);
-    return __builtin_amdgcn_alignbit(v[1], v[0], sh);
+    return u32x2{v[0], v[1]};
 }
 
 // Bins lo + 32j + i of a token row when lo is a multiple of 32: one row word.
@@ -208,6 +204,36 @@ __device__ __forceinline__ uint32_t row_word(__amdgpu_buffer_rsrc_t rs, uint32_t
     return __builtin_amdgcn_raw_buffer_load_b32(rs, byte_off, 0, 0);
 }
 
+// The row words of N tokens for one column.  ALIGNED: one word each; else two,
+// joined by a funnel shift once all of them are asked for (bits taken from
+// beyond a row's end belong to bins >= n_bins, which the caller masks).
+template <int N, bool OFF32, bool ALIGNED>
+__device__ __forceinline__ void load_rows(uint32_t (&w)[N], const uint32_t *toks,
+                                          __amdgpu_buffer_rsrc_t rs, const char *__restrict__ rows,
+                                          uint64_t row_bytes, uint32_t bo, uint32_t sh)
+{
+    if constexpr (ALIGNED) {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            w[u] = OFF32 ? row_word(rs, toks[u] + bo)
+                         : row_word(rows + (uint64_t)toks[u] * row_bytes, bo);
+    } else {
+        u32x2 v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            v[u] = OFF32 ? row_pair(rs, toks[u] + bo)
+                         : row_pair(rows + (uint64_t)toks[u] * row_bytes, bo);
+        // left to itself the compiler shifts each pair as it arrives, and where
+        // registers are short asks for one or two at a time (16 planes, 5000
+        // reads of 1000-2000 bases x 1-6000 bins: 986 us, 618 with all 16 in
+        // flight; 64-bit row offsets, 200 reads x 50000 bins: 597, 144)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            w[u] = __builtin_amdgcn_alignbit(v[u][1], v[u][0], sh);
+    }
+}
+
 // Adds the row bits of tokens [i0, i1) for one column into its counter.
 // ALIGNED: the window starts on a row word (sh = 0), so a column is one word
 // of each row and a wavefront's loads cover whole 256-byte runs.
@@ -217,32 +243,25 @@ __device__ __forceinline__ void add_rows(SlicedCount<NP> &c, const uint32_t *tok
                                          const char *__restrict__ rows, uint64_t row_bytes,
                                          uint32_t bo, uint32_t sh)
 {
-    auto load = [&](uint32_t tk) -> uint32_t {
-        if (OFF32)
-            return ALIGNED ? row_word(rs, tk + bo) : row_bins(rs, tk + bo, sh);
-        const char *row = rows + (uint64_t)tk * row_bytes;
-        return ALIGNED ? row_word(row, bo) : row_bins(row, bo, sh);
-    };
     uint32_t i = i0;
     for (; i + 16 <= i1; i += 16) {
         uint32_t w[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            w[u] = load(toks[i + u]);
+        load_rows<16, OFF32, ALIGNED>(w, toks + i, rs, rows, row_bytes, bo, sh);
         c.add16(w);
     }
     for (; i + 4 <= i1; i += 4) {
         uint32_t w[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            w[u] = load(toks[i + u]);
+        load_rows<4, OFF32, ALIGNED>(w, toks + i, rs, rows, row_bytes, bo, sh);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             c.add(w[u]);
     }
 #pragma unroll 1
-    for (; i < i1; ++i)
-        c.add(load(toks[i]));
+    for (; i < i1; ++i) {
+        uint32_t w[1];
+        load_rows<1, OFF32, ALIGNED>(w, toks + i, rs, rows, row_bytes, bo, sh);
+        c.add(w[0]);
+    }
 }
 
 // Which slots a workgroup works on.  The slots (reads, or places of the
@@ -325,6 +344,24 @@ __device__ __forceinline__ WindowRead load_window_read(const WindowArgs &a, uint
     return m;
 }
 
+__device__ __forceinline__ uint32_t win_uniform(uint32_t x)
+{
+    return __builtin_amdgcn_readfirstlane(x);
+}
+
+__device__ __forceinline__ uint64_t win_uniform(uint64_t x)
+{
+    return (uint64_t)win_uniform((uint32_t)(x >> 32)) << 32 | win_uniform((uint32_t)x);
+}
+
+// The same read in scalar registers: it is the whole workgroup's, and the vector
+// registers are the row loads'.
+__device__ __forceinline__ WindowRead win_uniform(const WindowRead &m)
+{
+    return {win_uniform(m.r), win_uniform(m.p0), win_uniform(m.p1), win_uniform(m.off),
+            win_uniform(m.L), win_uniform(m.lo), win_uniform(m.e)};
+}
+
 // One workgroup per read; the window of read r is bins [win_lo[r], win_lo[r] +
 // size) with size = cand_off[r+1] - cand_off[r], and pair cand_off[r] + j is bin
 // win_lo[r] + j.  Column j of a
@@ -369,7 +406,7 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
     if ((blockIdx.x >> shards.shift) >= shards.size(cur))
         return;
     uint32_t slot = cur * shards.per + (blockIdx.x >> shards.shift);
-    WindowRead rd = load_window_read(a, slot), next = {};
+    WindowRead rd = win_uniform(load_window_read(a, slot)), next = {};
     for (;;) {
         uint32_t drawn = 0;
         // the draw's slot, for the whole workgroup after its next barrier
@@ -572,7 +609,7 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
         }
         if (slot == kNoSlot)
             break;
-        rd = next;
+        rd = win_uniform(next);
     }
     if (t == 0 && skipped)
         atomicOr(a.status, skipped);
