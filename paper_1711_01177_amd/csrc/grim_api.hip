@@ -988,7 +988,7 @@ extern "C" int grim_filter_windows(const grim_index_t *idx, const grim_batch_t *
     a.counts = counts;
     a.pass_bits = pass_bits;
     a.status = reinterpret_cast<uint32_t *>(workspace);
-    a.counter = reinterpret_cast<uint32_t *>(workspace) + 1;
+    a.counters = reinterpret_cast<uint64_t *>(a.status + kWindowFirst);
     a.npl = planes_for(idx->q, b->max_len);
     HIP_TRY(launch_zero2(s, a.status, kWsHeader / 4, pass_bits, (b->n_pairs + 31) / 32));
     if (b->n_reads == 0)

@@ -21,7 +21,8 @@ constexpr uint32_t kTicketStride = 16;
 // The same for the bin-window kernel, one counter per XCD; all of the header's
 // words are zeroed before it runs.
 constexpr uint32_t kWindowShards = 8;
-constexpr uint32_t kWindowStride = 7;
+constexpr uint32_t kWindowFirst = 2;      // word of the header, 8-byte aligned
+constexpr uint32_t kWindowStride = 4;     // in 64-bit counters
 
 // Arguments of both filter kernels (passed by value).
 struct FilterArgs {
@@ -99,7 +100,7 @@ struct WindowArgs {
     int32_t *counts;
     uint32_t *pass_bits;
     uint32_t *status;
-    uint32_t *counter;          // kWindowShards words, kWindowStride words apart
+    uint64_t *counters;         // kWindowShards of them, kWindowStride apart
     int npl;
 };
 

@@ -205,8 +205,12 @@ __device__ __forceinline__ uint32_t row_word(__amdgpu_buffer_rsrc_t rs, uint32_t
 }
 
 // The row words of N tokens for one column.  ALIGNED: one word each; else two,
-// joined by a funnel shift once all of them are asked for (bits taken from
-// beyond a row's end belong to bins >= n_bins, which the caller masks).
+// joined by a funnel shift (bits taken from beyond a row's end belong to bins
+// >= n_bins, which the caller masks).  All of them are asked for before the first
+// is used: left to itself the compiler shifts or adds each as it arrives, and
+// where registers are short asks for one or two at a time (16 planes, 5000 reads
+// of 1000-2000 bases x 1-6000 bins: 986 us, 618 with all 16 in flight; 64-bit row
+// offsets, 200 reads x 50000 bins: 597, 144).
 template <int N, bool OFF32, bool ALIGNED>
 __device__ __forceinline__ void load_rows(uint32_t (&w)[N], const uint32_t *toks,
                                           __amdgpu_buffer_rsrc_t rs, const char *__restrict__ rows,
@@ -217,16 +221,13 @@ __device__ __forceinline__ void load_rows(uint32_t (&w)[N], const uint32_t *toks
         for (int u = 0; u < N; ++u)
             w[u] = OFF32 ? row_word(rs, toks[u] + bo)
                          : row_word(rows + (uint64_t)toks[u] * row_bytes, bo);
+        __builtin_amdgcn_sched_barrier(0);
     } else {
         u32x2 v[N];
 #pragma unroll
         for (int u = 0; u < N; ++u)
             v[u] = OFF32 ? row_pair(rs, toks[u] + bo)
                          : row_pair(rows + (uint64_t)toks[u] * row_bytes, bo);
-        // left to itself the compiler shifts each pair as it arrives, and where
-        // registers are short asks for one or two at a time (16 planes, 5000
-        // reads of 1000-2000 bases x 1-6000 bins: 986 us, 618 with all 16 in
-        // flight; 64-bit row offsets, 200 reads x 50000 bins: 597, 144)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -269,9 +270,22 @@ __device__ __forceinline__ void add_rows(SlicedCount<NP> &c, const uint32_t *tok
 // workgroups of one XCD (blockIdx % 8) then work on neighbouring windows, whose
 // row segments meet in its L2.  A workgroup's first slot is its own number in
 // its shard, later ones are drawn from the shard's counter (11.4 ns a draw for
-// the whole GPU with one counter, 4.8 with these), and once that is used up from
-// the shard with most left.
+// the whole GPU with one counter, 4.8 with these).
+//
+// A workgroup whose shard is used up helps another one that still has more than
+// a slot for each of its own workgroups.  Most workgroups come to that point at
+// the same time, and whatever they read or add on the counters' lines is served
+// one after another, so a draw brings the answer with it: the low half of a
+// counter counts draws, and the draw that leaves a shard with just a slot for
+// each workgroup sets the shard's bit in the high half of every counter.  (5000
+// reads x 4096 bins 88 us, of 1-3000 bins 56; with one more word to read at the end
+// 104 and 71, with all counters looked over for the one with most left 111 and 84.)
 constexpr uint32_t kNoSlot = ~0u;
+
+__device__ __forceinline__ uint64_t window_draw(uint64_t *counter)
+{
+    return atomicAdd(reinterpret_cast<unsigned long long *>(counter), 1ull);
+}
 
 struct Shards {
     uint32_t n, per, shift;
@@ -290,36 +304,39 @@ struct Shards {
     {
         return (gridDim.x + (1u << shift) - 1 - s) >> shift;
     }
-    // the slot of a draw from shard cur that gave k (lane 0's), or another
-    // shard's, or kNoSlot; one wavefront
-    __device__ __forceinline__ uint32_t slot(uint32_t k, uint32_t *counters, uint32_t &cur,
+    // the slot of a draw from shard cur (lane 0's), or kNoSlot; one wavefront
+    __device__ __forceinline__ uint32_t of_draw(uint64_t draw, uint64_t *counters, uint32_t cur,
+                                                int lane) const
+    {
+        const uint32_t at = groups(cur) + __builtin_amdgcn_readfirstlane((uint32_t)draw);
+        if (at + groups(cur) == size(cur) && lane < (1 << shift))
+            atomicOr(reinterpret_cast<unsigned long long *>(&counters[lane * kWindowStride]),
+                     1ull << (32 + cur));
+        return at < size(cur) ? cur * per + at : kNoSlot;
+    }
+    // the same, or another shard's where that is used up
+    __device__ __forceinline__ uint32_t slot(uint64_t draw, uint64_t *counters, uint32_t &cur,
                                              int lane) const
     {
-        k = groups(cur) + __builtin_amdgcn_readfirstlane(k);
-        if (k < size(cur))
-            return cur * per + k;
-        // used up: the shard with most left (if another workgroup is faster, its
-        // own ones still drain it)
-        uint32_t left = 0;
-        if (lane < (1 << shift)) {
-            const uint32_t gone =
-                groups(lane) + __hip_atomic_load(&counters[lane * kWindowStride], __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-            left = size(lane) > gone ? size(lane) - gone : 0u;
-        }
-        uint32_t most = left;
-#pragma unroll
-        for (int m = 4; m >= 1; m >>= 1)
-            most = max(most, (uint32_t)__shfl_xor(most, m));
-        most = __builtin_amdgcn_readfirstlane(most);
-        if (!most)
+        const uint32_t mine = of_draw(draw, counters, cur, lane);
+        if (mine != kNoSlot)
+            return mine;
+        // shards of two slots a workgroup or more, and not marked
+        const uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)(draw >> 32));
+        const uint32_t open =
+            (uint32_t)__ballot(lane < (1 << shift) && (uint32_t)lane != cur &&
+                               size(lane) >= 2 * groups(lane)) & ~low;
+        if (!open)
             return kNoSlot;
-        cur = (uint32_t)__builtin_ctzll(__ballot(lane < (1 << shift) && left == most));
-        k = 0;
+        // the next one from a place of its own on, so that helpers spread
+        const uint32_t from = (blockIdx.x >> shift) & ((1u << shift) - 1);
+        const uint32_t after = open >> from << from;
+        cur = (uint32_t)__builtin_ctz(after ? after : open);
+        uint64_t again = 0;
         if (lane == 0)
-            k = atomicAdd(&counters[cur * kWindowStride], 1u);
-        k = groups(cur) + __builtin_amdgcn_readfirstlane(k);
-        return k < size(cur) ? cur * per + k : kNoSlot;
+            again = window_draw(&counters[cur * kWindowStride]);
+        // if others were faster, the shard's own workgroups still drain it
+        return of_draw(again, counters, cur, lane);
     }
 };
 
@@ -372,19 +389,23 @@ __device__ __forceinline__ WindowRead win_uniform(const WindowRead &m)
 // bit-sliced ripple adder, pass bits come from a bit-sliced comparison with T,
 // and the counts are unpacked into LDS so that their stores are coalesced.
 // A wavefront's loads return behind its earlier stores, so the next read is drawn
-// before a read's rows are added and its offsets are asked for before its counts
-// are stored.
+// and its offsets are asked for before a read's counts are stored; the draw waits
+// until its rows are added, so that a workgroup behind the others does not hold
+// a second read.
 // NP: bit planes per counter (8 covers reads of up to 2^8 + q - 2 bases, else 16).
 // OFF32: the row buffer is below 4 GiB; LDS then holds each token's row byte
 // offset instead of the token.
 //
-// Measured: 200k reads x 4096 bins in processing order 2.53 ms (2.79 with every
-// slot drawn from one counter and loads behind the stores), 100k of 1-2000 bins
-// 0.87 ms (1.25), 20k of 1-64 bins 156 us (257: 128 columns and two parts for
-// every window); starting anywhere, 200k x 4096 3.49 ms (3.48), 5000 of 1-3000
-// bins 85 us (88), of 1-6000 111 us (107).
+// Four wavefronts a SIMD (128 registers), three where two address words a row and
+// 16 planes would leave too few for the loads.
+//
+// Measured (before: every slot drawn from one counter, loads behind the stores, 128
+// columns and two parts for every window): 200k reads x 4096 bins in processing
+// order 2.47 ms (2.79); starting anywhere, 100k of 1-3000 bins 1.24 ms (1.48), 200k
+// of 64 bins 1.45 ms (2.37), 5000 of 1-3000 bins 56 us (87), of 1-6000 81 us (104);
+// q = 7, 5000 reads of 1000-2000 bases x 1-6000 bins 607 us (650).
 template <int Q, int NP, bool OFF32>
-__global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
+__global__ __launch_bounds__(256, NP == 8 || OFF32 ? 4 : 3) void window_kernel(WindowArgs a)
 {
     typedef typename std::conditional<NP == 8, uint8_t, uint16_t>::type cnt_t;
     constexpr int CPW = 4 / sizeof(cnt_t);          // counts per LDS word
@@ -408,11 +429,11 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
     uint32_t slot = cur * shards.per + (blockIdx.x >> shards.shift);
     WindowRead rd = win_uniform(load_window_read(a, slot)), next = {};
     for (;;) {
-        uint32_t drawn = 0;
+        uint64_t drawn = 0;
         // the draw's slot, for the whole workgroup after its next barrier
         auto publish = [&]() {
             if (t < 64) {
-                const uint32_t s = shards.slot(drawn, a.counter, cur, t);
+                const uint32_t s = shards.slot(drawn, a.counters, cur, t);
                 if (t == 0)
                     next_slot = s;
             }
@@ -447,8 +468,8 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
             const uint32_t tk = win_token_at<Q>(a.rw, a.nw, off + i);
             toks[i] = OFF32 ? tk * (uint32_t)row_bytes : tk;
         }
-        if (t == 0)
-            drawn = atomicAdd(&a.counter[cur * kWindowStride], 1u);
+        if (!valid && t == 0)
+            drawn = window_draw(&a.counters[cur * kWindowStride]);
         __syncthreads();
         if (!valid) {
             publish();
@@ -483,8 +504,8 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
                     add_rows<NP, OFF32, false>(c, toks, i0, i1, rs, rows, row_bytes, bo, sh);
             }
             const bool last_round = vb + 128 >= n_cols;
-            if (last_round)
-                publish();
+            if (last_round && t == 0)
+                drawn = window_draw(&a.counters[cur * kWindowStride]);
             // parts [s, 2 s) are added to parts [0, s)
             for (uint32_t s = n_parts / 2; s >= 1; s /= 2) {
                 if (part >= s && part < 2 * s) {
@@ -560,6 +581,8 @@ __global__ __launch_bounds__(256) void window_kernel(WindowArgs a)
                     }
                 }
             }
+            if (last_round)
+                publish();
             __syncthreads();
             if (last_round)
                 take_next();
