@@ -461,6 +461,100 @@ __device__ __forceinline__ int32_t column_scan_from(int s, const uint64_t *peq_t
     return column_scan<NW, S, UNI>(peq_t, pv, mv, rp, wsh, span, L);
 }
 
+// Distance of survivor i from the scan of all columns (-1 for a read or bin id out
+// of range), by thread t; *ok is set where it is within the read's tolerance.
+// peq: room for the match masks of every thread's read, peq[(base * W + block) *
+// 256 + thread], block = rows 64 block .. 64 block + 63 of the bottom-aligned
+// vector (lane-interleaved, so that a wavefront's reads of one column are
+// conflict-free whatever bases its lanes see).
+template <int W>
+__device__ __forceinline__ int32_t scan_survivor(const VerifyArgs &a, uint64_t i, uint64_t *peq,
+                                                 int t, bool *ok)
+{
+    constexpr int NW = 2 * W;
+    const uint64_t nb = a.nw * 16;
+    const uint32_t r = a.surv_read[i], b = a.surv_bin[i];
+    const uint32_t L = r < a.n_reads ? a.read_len[r] : 0u;
+    const uint64_t off = r < a.n_reads ? a.read_off[r] : 0u;
+    if (r < a.n_reads && b < a.n_bins && L <= 32u * NW && off <= nb &&
+        L <= nb - off) {
+        const uint32_t E =
+            (uint32_t)(((uint64_t)a.read_e[r] * L + a.e_den - 1) / a.e_den);
+        const int pad = 32 * NW - (int)L;   // rows above the read
+        uint32_t pv[NW], mv[NW];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            // 16 rows at a time: rows 64 w + 16 g + k (k = 0..15) hold
+            // read bases i0 + k, i0 = 64 w + 16 g - pad; rows with
+            // i0 + k < 0 match every base
+            uint32_t ma[2] = {0u, 0u}, mc[2] = {0u, 0u}, mg[2] = {0u, 0u},
+                     mt[2] = {0u, 0u}, pw[2] = {~0u, ~0u};
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int i0 = 64 * w + 16 * g - pad;
+                const uint32_t sh = 16 * (g & 1);
+                const int half = g >> 1;
+                uint32_t xa = 0xFFFFu, xc = 0xFFFFu, xg = 0xFFFFu, xt = 0xFFFFu,
+                         pm = 0xFFFFu;
+                if (i0 > -16) {
+                    pm = i0 >= 0 ? 0u : (1u << -i0) - 1u;
+                    // base k in bits 2k (high bit of its code) and 2k + 1 (low bit)
+                    const uint32_t rv = __builtin_bitreverse32(
+                        read_window(a.rw, a.nw, (int64_t)off + i0));
+                    const uint32_t h = rv & 0x55555555u, l = (rv >> 1) & 0x55555555u;
+                    xa = even_bits(~(h | l) & 0x55555555u) | pm;
+                    xc = even_bits(l & ~h) | pm;
+                    xg = even_bits(h & ~l) | pm;
+                    xt = even_bits(h & l) | pm;
+                }
+                ma[half] |= xa << sh;
+                mc[half] |= xc << sh;
+                mg[half] |= xg << sh;
+                mt[half] |= xt << sh;
+                pw[half] &= ~(pm << sh);
+            }
+            peq[(0 * W + w) * 256 + t] = (uint64_t)ma[1] << 32 | ma[0];
+            peq[(1 * W + w) * 256 + t] = (uint64_t)mc[1] << 32 | mc[0];
+            peq[(2 * W + w) * 256 + t] = (uint64_t)mg[1] << 32 | mg[0];
+            peq[(3 * W + w) * 256 + t] = (uint64_t)mt[1] << 32 | mt[0];
+            pv[2 * w] = pw[0];
+            pv[2 * w + 1] = pw[1];
+            mv[2 * w] = mv[2 * w + 1] = 0u;
+        }
+        const uint64_t lo = (uint64_t)b * a.B;
+        uint64_t hi = lo + a.B + a.O;
+        if (hi > a.G)
+            hi = a.G;
+        // an empty read matches anywhere with no edits: no columns
+        const uint64_t span = hi > lo && L > 0 ? hi - lo : 0;
+        // the wavefront's first word: the most words any of its
+        // scanning lanes needs, counted from the bottom
+        const uint32_t n = (L + 31) >> 5;
+        int nmax = 0;
+#pragma unroll
+        for (int v = 1; v <= NW; ++v)
+            nmax += __builtin_amdgcn_ballot_w64(n >= (uint32_t)v) != 0;
+        // 16 reference bases are fetched every 16 columns; their bit
+        // offset inside the first packed word is the span start's,
+        // the same at every fetch.
+        const uint32_t *rp = a.ref + (lo >> 4);
+        const uint32_t wsh = ((uint32_t)lo & 15u) << 1;
+        // one span for all scanning lanes (all but the last bin's)?
+        const uint32_t s_lo = __builtin_amdgcn_readfirstlane((uint32_t)span);
+        const uint32_t s_hi = __builtin_amdgcn_readfirstlane((uint32_t)(span >> 32));
+        const bool uni = __builtin_amdgcn_ballot_w64(
+                             span != ((uint64_t)s_hi << 32 | s_lo)) == 0;
+        const int32_t best =
+            uni ? column_scan_from<NW, 0, true>(NW - nmax, peq + t, pv, mv, rp, wsh,
+                                                span, (int32_t)L)
+                : column_scan_from<NW, 0, false>(NW - nmax, peq + t, pv, mv, rp,
+                                                 wsh, span, (int32_t)L);
+        *ok = best <= (int32_t)E;
+        return min<int32_t>(best, (int32_t)E + 1);
+    }
+    return -1;
+}
+
 // ------------------------------------------- location check by exact pieces
 // A read of L bases aligned with at most E edits, cut into E + 1 disjoint
 // pieces, has one that no edit touches: it occurs unchanged in the span, and the
@@ -716,16 +810,26 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
 // collected in LDS as twice the distance, or 2 E + 1 while none within E is
 // known; distances and pass bits leave together.  W is the number of 64-row
 // blocks (NW = 2 W words) the batch's longest read needs.
+//
+// SCAN: phase C is the end of the same kernel (short lists, where a second launch
+// costs more than it saves).  Else it is verify_scan_kernel's, for the survivors
+// marked with kScanMark in place of a distance: beside phase A's registers and
+// LDS the scan has 3 wavefronts a SIMD, by itself 8 (4 and 2 for reads of over
+// 128 and 256 bases), and idle ones in chunks of which only a part comes to it
+// (2.5e6 survivors of 100 bases at 15 % edits 1.28 ms, 1.48 in one kernel, 1.33 with
+// the scan alone for every survivor; of 64-250 bases at 8 and 15 % 1.90, 2.30 and
+// 1.99).
 constexpr int kVerifyChunk = 1024;
 constexpr int kVerifySmall = 256;
+constexpr int32_t kScanMark = INT32_MIN;
 
-template <int W, int CH>
+template <int W, int CH, bool SCAN>
 __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a)
 {
     constexpr int NW = 2 * W;
-    constexpr int kKeys = kPieces + NW + 2;   // edits | words | past the chunk's end
+    constexpr int kKeys = kPieces + (SCAN ? NW : 0) + 2;   // edits | words | past the chunk's end
     constexpr uint32_t kSettled = ~0u;        // written to memory already
-    constexpr uint32_t kBands = CH + CH / 2, kBroad = W > 4 && CH > 256 ? 128 : 512;
+    constexpr uint32_t kBands = CH + CH / 2, kBroad = 512;
     constexpr int U = CH / 256;   // slots per thread
     static_assert(kKeys <= 64, "one wavefront scans the keys");
     __shared__ uint16_t order[CH];
@@ -737,12 +841,8 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
     __shared__ uint16_t rest[CH];             // survivors of phase A for phase C
     __shared__ uint32_t n_bands, n_narrow, n_wide, n_broad, n_rest;
     __shared__ uint32_t next_a, next_b;       // wavefront runs of phases A and B handed out
-    // phase A: pieces[piece * 256 + thread]; phase C: the match masks of every
-    // thread's read, peq[(base * W + block) * 256 + thread], block = rows 64
-    // block .. 64 block + 63 of the bottom-aligned vector (lane-interleaved, so
-    // that a wavefront's reads of one column are conflict-free whatever bases
-    // its lanes see)
-    __shared__ uint64_t peq[(W > 4 ? 4 * W : 16) * 256];
+    // phase A: pieces[piece * 256 + thread]; phase C: match masks
+    __shared__ uint64_t peq[(SCAN && W > 4 ? 4 * W : 16) * 256];
     uint32_t *pieces = reinterpret_cast<uint32_t *>(peq);
     const int t = threadIdx.x, lane = t & 63;
     auto draw = [&](uint32_t *next) -> uint32_t {
@@ -751,6 +851,7 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
             x = atomicAdd(next, 1u);
         return __builtin_amdgcn_readfirstlane(x);
     };
+    const uint32_t max_rows = SCAN ? 32u * NW : a.max_rows;
     const uint64_t nb = a.nw * 16;
     const uint64_t per = ((a.n_surv + gridDim.x - 1) / gridDim.x + 31) & ~31ull;
     const uint64_t g0 = (uint64_t)blockIdx.x * per;
@@ -785,11 +886,11 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
                 const uint32_t r = a.surv_read[base + p], b = a.surv_bin[base + p];
                 if (r < a.n_reads) {
                     const uint32_t L = a.read_len[r];
-                    if (L <= 32u * NW)
+                    if (SCAN && L <= max_rows)
                         k = kPieces + (int)((L + 31) >> 5);
                     const uint64_t off = a.read_off[r];
                     const uint64_t E = ((uint64_t)a.read_e[r] * L + a.e_den - 1) / a.e_den;
-                    if (b < a.n_bins && L <= 32u * NW && off <= nb && L <= nb - off &&
+                    if (b < a.n_bins && L <= max_rows && off <= nb && L <= nb - off &&
                         E < (uint64_t)kPieces && L >= (E + 1) * kPieceMin &&
                         span_all <= (uint64_t)kSpanMax) {
                         k = (int)E;
@@ -816,7 +917,12 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
 #pragma unroll
         for (int u = 0; u < U; ++u)
             order[cls[key[u]] + rank[u]] = (uint16_t)(u * 256 + t);
-        const uint32_t n_pieces = cls[kPieces];   // survivors of phase A
+        // survivors of phase A; where they are few they go to the scan as well: a
+        // chunk with 141 of 1024 takes 100 us here, its wavefronts one run each and
+        // the others waiting, and their scan no longer
+        uint32_t n_pieces = __builtin_amdgcn_readfirstlane(cls[kPieces]);
+        if (!SCAN && n_pieces * 6 < cnt)
+            n_pieces = 0;
         __syncthreads();
 
         // ------------------------------------------------ phase A: pieces
@@ -916,92 +1022,13 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
         const uint32_t n_all = cls[kKeys - 1] - n_pieces;   // survivors without pieces
         for (uint32_t x = t; x < n_all + n_rest; x += 256) {
             const uint32_t slot = x < n_all ? order[n_pieces + x] : rest[x - n_all];
-            const uint64_t i = base + slot;
-            {
-                int32_t d = -1;
+            if constexpr (SCAN) {
                 bool ok = false;
-                const uint32_t r = a.surv_read[i], b = a.surv_bin[i];
-                const uint32_t L = r < a.n_reads ? a.read_len[r] : 0u;
-                const uint64_t off = r < a.n_reads ? a.read_off[r] : 0u;
-                if (r < a.n_reads && b < a.n_bins && L <= 32u * NW && off <= nb &&
-                    L <= nb - off) {
-                    const uint32_t E =
-                        (uint32_t)(((uint64_t)a.read_e[r] * L + a.e_den - 1) / a.e_den);
-                    const int pad = 32 * NW - (int)L;   // rows above the read
-                    uint32_t pv[NW], mv[NW];
-#pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        // 16 rows at a time: rows 64 w + 16 g + k (k = 0..15) hold
-                        // read bases i0 + k, i0 = 64 w + 16 g - pad; rows with
-                        // i0 + k < 0 match every base
-                        uint32_t ma[2] = {0u, 0u}, mc[2] = {0u, 0u}, mg[2] = {0u, 0u},
-                                 mt[2] = {0u, 0u}, pw[2] = {~0u, ~0u};
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            const int i0 = 64 * w + 16 * g - pad;
-                            const uint32_t sh = 16 * (g & 1);
-                            const int half = g >> 1;
-                            uint32_t xa = 0xFFFFu, xc = 0xFFFFu, xg = 0xFFFFu, xt = 0xFFFFu,
-                                     pm = 0xFFFFu;
-                            if (i0 > -16) {
-                                pm = i0 >= 0 ? 0u : (1u << -i0) - 1u;
-                                // base k in bits 2k (high bit of its code) and 2k + 1 (low bit)
-                                const uint32_t rv = __builtin_bitreverse32(
-                                    read_window(a.rw, a.nw, (int64_t)off + i0));
-                                const uint32_t h = rv & 0x55555555u, l = (rv >> 1) & 0x55555555u;
-                                xa = even_bits(~(h | l) & 0x55555555u) | pm;
-                                xc = even_bits(l & ~h) | pm;
-                                xg = even_bits(h & ~l) | pm;
-                                xt = even_bits(h & l) | pm;
-                            }
-                            ma[half] |= xa << sh;
-                            mc[half] |= xc << sh;
-                            mg[half] |= xg << sh;
-                            mt[half] |= xt << sh;
-                            pw[half] &= ~(pm << sh);
-                        }
-                        peq[(0 * W + w) * 256 + t] = (uint64_t)ma[1] << 32 | ma[0];
-                        peq[(1 * W + w) * 256 + t] = (uint64_t)mc[1] << 32 | mc[0];
-                        peq[(2 * W + w) * 256 + t] = (uint64_t)mg[1] << 32 | mg[0];
-                        peq[(3 * W + w) * 256 + t] = (uint64_t)mt[1] << 32 | mt[0];
-                        pv[2 * w] = pw[0];
-                        pv[2 * w + 1] = pw[1];
-                        mv[2 * w] = mv[2 * w + 1] = 0u;
-                    }
-                    const uint64_t lo = (uint64_t)b * a.B;
-                    uint64_t hi = lo + a.B + a.O;
-                    if (hi > a.G)
-                        hi = a.G;
-                    // an empty read matches anywhere with no edits: no columns
-                    const uint64_t span = hi > lo && L > 0 ? hi - lo : 0;
-                    // the wavefront's first word: the most words any of its
-                    // scanning lanes needs, counted from the bottom
-                    const uint32_t n = (L + 31) >> 5;
-                    int nmax = 0;
-#pragma unroll
-                    for (int v = 1; v <= NW; ++v)
-                        nmax += __builtin_amdgcn_ballot_w64(n >= (uint32_t)v) != 0;
-                    // 16 reference bases are fetched every 16 columns; their bit
-                    // offset inside the first packed word is the span start's,
-                    // the same at every fetch.
-                    const uint32_t *rp = a.ref + (lo >> 4);
-                    const uint32_t wsh = ((uint32_t)lo & 15u) << 1;
-                    // one span for all scanning lanes (all but the last bin's)?
-                    const uint32_t s_lo = __builtin_amdgcn_readfirstlane((uint32_t)span);
-                    const uint32_t s_hi = __builtin_amdgcn_readfirstlane((uint32_t)(span >> 32));
-                    const bool uni = __builtin_amdgcn_ballot_w64(
-                                         span != ((uint64_t)s_hi << 32 | s_lo)) == 0;
-                    const int32_t best =
-                        uni ? column_scan_from<NW, 0, true>(NW - nmax, peq + t, pv, mv, rp, wsh,
-                                                            span, (int32_t)L)
-                            : column_scan_from<NW, 0, false>(NW - nmax, peq + t, pv, mv, rp,
-                                                             wsh, span, (int32_t)L);
-                    d = min<int32_t>(best, (int32_t)E + 1);
-                    ok = best <= (int32_t)E;
-                }
-                a.dist[i] = d;
+                a.dist[base + slot] = scan_survivor<W>(a, base + slot, peq, t, &ok);
                 if (ok)
                     atomicOr(&okw[slot >> 5], 1u << (slot & 31));
+            } else {
+                a.dist[base + slot] = kScanMark;
             }
         }
         // distances of phases A and B
@@ -1017,6 +1044,67 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
         __syncthreads();
         if (t < (int)((cnt + 31) / 32))
             a.ok_bits[(base >> 5) + t] = okw[t];
+        __syncthreads();
+    }
+}
+
+// Phase C by itself, in ranges like verify_kernel's and chunks of 256: the
+// survivors that kernel marked (ALL: every survivor, of batches it is not run on),
+// sorted by the number of 32-row words of their read (counting sort in LDS) so
+// that a wavefront starts at one word.  Chunks of 1024 sort better but leave the
+// last round of workgroups nearly empty (5e5 survivors of 100 bases at 15 % edits
+// 359 us, 512 248, 256 223; 2.5e6 of 100-250 bases 2.09 ms, 1.96, 1.85).
+template <int W, bool ALL>
+__global__ __launch_bounds__(256, W <= 2 ? 8 : W <= 4 ? 4 : 2) void verify_scan_kernel(VerifyArgs a)
+{
+    constexpr int NW = 2 * W;
+    constexpr uint32_t CH = kVerifySmall;
+    __shared__ uint16_t order[CH];
+    __shared__ uint32_t cls[NW + 1], okw[CH / 32];
+    __shared__ uint64_t peq[4 * W * 256];
+    const uint32_t t = threadIdx.x;
+    const uint64_t per = ((a.n_surv + gridDim.x - 1) / gridDim.x + 31) & ~31ull;
+    const uint64_t g0 = (uint64_t)blockIdx.x * per;
+    const uint64_t g1 = g0 + per < a.n_surv ? g0 + per : a.n_surv;
+    for (uint64_t base = g0; base < g1; base += CH) {
+        const uint32_t cnt = (uint32_t)(g1 - base < CH ? g1 - base : CH);
+        const bool mine = t < cnt && (ALL || a.dist[base + t] == kScanMark);
+        if (!__syncthreads_or(mine))
+            continue;
+        if (t < NW + 1)
+            cls[t] = 0;
+        if (t < CH / 32)
+            okw[t] = 0;
+        __syncthreads();
+        // class of survivor t: its read's word count, 0 when there is nothing to align
+        uint32_t key = 0, rank = 0;
+        if (mine) {
+            const uint32_t r = a.surv_read[base + t];
+            const uint32_t L = r < a.n_reads ? a.read_len[r] : 0u;
+            key = L <= 32u * NW ? (L + 31) >> 5 : 0u;
+            rank = atomicAdd(&cls[key], 1u);
+        }
+        __syncthreads();
+        uint32_t before = 0, n = 0;
+        for (uint32_t c = 0; c <= (uint32_t)NW; ++c) {
+            before += c < key ? cls[c] : 0u;
+            n += cls[c];
+        }
+        if (mine)
+            order[before + rank] = (uint16_t)t;
+        __syncthreads();
+        if (t < n) {
+            const uint32_t slot = order[t];
+            bool ok = false;
+            a.dist[base + slot] = scan_survivor<W>(a, base + slot, peq, t, &ok);
+            if (ok)
+                atomicOr(&okw[slot >> 5], 1u << (slot & 31));
+        }
+        __syncthreads();
+        if (t < (cnt + 31) / 32) {
+            uint32_t *w = &a.ok_bits[(base >> 5) + t];   // this workgroup's alone
+            *w = ALL ? okw[t] : *w | okw[t];
+        }
         __syncthreads();
     }
 }
@@ -1045,50 +1133,66 @@ hipError_t launch_planes(hipStream_t s, const uint32_t *ref, uint64_t nw, uint2 
     return hipGetLastError();
 }
 
-hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a)
+// Launches kernel k over the survivors, a sorted chunk per workgroup, dispatched as
+// resident ones finish; past 64 times the resident count each takes a run of whole
+// chunks.  resident: workgroups a CU holds (LDS or register bound), asked once per
+// kernel and process; it only sizes the grid's cap, never what is computed.
+static hipError_t launch_chunks(hipStream_t s, const void *k, std::atomic<int> &resident, int cus,
+                                uint64_t chunk, const VerifyArgs &a)
 {
-    VerifyArgs copy = a;
-    void *args[] = {&copy};
-    // chunks of 1024 sort and pack better (2.5M survivors: 512 9 % slower; 5.3e5:
-    // 246 us, 256 327 us); lists that would leave CUs without one take chunks of
-    // 256 (7.3e4: 121 us; 64, the wavefronts sharing each survivor's pieces, 144)
-    const bool small = a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * kVerifyChunk;
-    const uint64_t chunk = small ? kVerifySmall : kVerifyChunk;
-    const void *k = nullptr;
-    int wi = 0;
-#define VERIFY_K(W)                                                                \
-    (small ? reinterpret_cast<const void *>(&verify_kernel<W, kVerifySmall>)       \
-           : reinterpret_cast<const void *>(&verify_kernel<W, kVerifyChunk>))
-    switch (W) {
-    case 1: k = VERIFY_K(1); wi = 0; break;
-    case 2: k = VERIFY_K(2); wi = 1; break;
-    case 4: k = VERIFY_K(4); wi = 2; break;
-    case 8: k = VERIFY_K(8); wi = 3; break;
-    default: return hipErrorInvalidValue;
-    }
-#undef VERIFY_K
-    wi = 2 * wi + small;
-    // workgroups resident per CU (LDS bound), asked once per kernel and
-    // process; it only sizes the grid's cap, never what is computed
-    static std::atomic<int> resident[8];
-    int per_cu = resident[wi].load(std::memory_order_relaxed);
+    int per_cu = resident.load(std::memory_order_relaxed);
     if (per_cu <= 0) {
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0);
         if (e != hipSuccess)
             return e;
         if (per_cu <= 0)
             per_cu = 1;
-        resident[wi].store(per_cu, std::memory_order_relaxed);
+        resident.store(per_cu, std::memory_order_relaxed);
     }
-    // one sorted chunk per workgroup, dispatched as resident ones finish;
-    // past 64 times the resident count, each takes a run of m whole chunks
     const uint64_t chunks = (a.n_surv + chunk - 1) / chunk;
     const uint64_t cap = (uint64_t)per_cu * (uint64_t)(cus > 0 ? cus : 1) * 64;
     const uint64_t m = (chunks + cap - 1) / cap;
     const uint64_t grid = (chunks + m - 1) / m;
     if (grid == 0)
         return hipSuccess;
+    VerifyArgs copy = a;
+    void *args[] = {&copy};
     return hipLaunchKernel(k, dim3((uint32_t)grid), dim3(256), args, 0, s);
+}
+
+template <int W>
+static hipError_t launch_verify_w(hipStream_t s, int cus, const VerifyArgs &a)
+{
+    static std::atomic<int> resident[4];
+    const void *all = reinterpret_cast<const void *>(&verify_scan_kernel<W, true>);
+    const void *marked = reinterpret_cast<const void *>(&verify_scan_kernel<W, false>);
+    const void *small = reinterpret_cast<const void *>(&verify_kernel<W, kVerifySmall, true>);
+    const void *large = reinterpret_cast<const void *>(&verify_kernel<1, kVerifyChunk, false>);
+    const uint64_t span = a.B + a.O < a.G ? a.B + a.O : a.G;
+    if (span > (uint64_t)kSpanMax)   // no survivor has pieces
+        return launch_chunks(s, all, resident[0], cus, kVerifySmall, a);
+    // chunks of 1024 sort and pack better (2.5M survivors: 512 9 % slower; 5.3e5:
+    // 246 us, 256 327 us); lists that would leave CUs without one take chunks of
+    // 256 (7.3e4: 121 us; 64, the wavefronts sharing each survivor's pieces, 144)
+    if (a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * kVerifyChunk)
+        return launch_chunks(s, small, resident[1], cus, kVerifySmall, a);
+    const hipError_t e = launch_chunks(s, large, resident[2], cus, kVerifyChunk, a);
+    if (e != hipSuccess)
+        return e;
+    return launch_chunks(s, marked, resident[3], cus, kVerifySmall, a);
+}
+
+hipError_t launch_verify(hipStream_t s, int W, int cus, const VerifyArgs &a)
+{
+    VerifyArgs b = a;
+    b.max_rows = 64u * (uint32_t)W;
+    switch (W) {
+    case 1: return launch_verify_w<1>(s, cus, b);
+    case 2: return launch_verify_w<2>(s, cus, b);
+    case 4: return launch_verify_w<4>(s, cus, b);
+    case 8: return launch_verify_w<8>(s, cus, b);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace grim

@@ -76,6 +76,7 @@ struct VerifyArgs {
     const uint32_t *surv_read;
     const uint32_t *surv_bin;
     uint64_t n_surv;
+    uint32_t max_rows;          // longest read the launched kernels take
     int32_t *dist;
     uint32_t *ok_bits;
 };
