@@ -178,15 +178,16 @@ __device__ __forceinline__ uint64_t read_of(const Off *off, uint64_t lo, uint64_
 }
 
 // A workgroup covers WPB words of the bitmask: a whole block of the count pass
-// (32768 pairs), or a sixteenth of one where there are too few blocks to fill the
-// chip, and then counts the words before its own in the block itself.  Its
+// (32768 pairs), or a quarter or a sixteenth of one where there are too few blocks
+// to fill the chip, and then counts the words before its own in the block itself.  Its
 // passing pairs are listed in LDS kEmitList at a time (about 490 a block at
 // 1.5 %), and the offsets of the reads they belong to, relative to its first
 // pair, are staged there when there are at most kStageReads of them.
 constexpr int kStageReads = 2048;
 constexpr int kEmitList = 4096;
 constexpr int kEmitRow = 4;       // survivors per thread whose bin ids load together
-constexpr int kEmitSmall = 64;    // words of a small workgroup
+constexpr int kEmitSmall = 64;    // words of the smaller workgroups
+constexpr int kEmitMiddle = 256;
 
 template <int WPB>
 __global__ __launch_bounds__(256) void compact_emit_kernel(
@@ -287,16 +288,21 @@ hipError_t launch_compact(hipStream_t s, const uint32_t *bits, uint64_t n_pairs,
     hipLaunchKernelGGL(compact_count_kernel, dim3((uint32_t)((nb + kCountBlocks - 1) / kCountBlocks)),
                        dim3(256), 0, s, bits, n_words, n_pairs, nb, block_sums);
     hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(1024), 0, s, block_sums, nb, n_out);
-    // below 128 blocks (4.2e6 pairs) in sixteenths, so that more CUs have one
-    if (nb < 128)
-        hipLaunchKernelGGL(compact_emit_kernel<kEmitSmall>,
-                           dim3((uint32_t)((n_words + kEmitSmall - 1) / kEmitSmall)), dim3(256), 0,
-                           s, bits, n_words, n_pairs, block_sums, cand_off, n_reads, cand_bin, cap,
-                           surv_pair, surv_read, surv_bin);
-    else
-        hipLaunchKernelGGL(compact_emit_kernel<kCompactWpb>, dim3((uint32_t)nb), dim3(256), 0, s,
+    // Sixteenths below 128 blocks (4.2e6 pairs), quarters below 512 (1.7e7).  All three
+    // launches, whole blocks / quarters / sixteenths: 4.3e6 pairs at 1.5 % passing 14 /
+    // 14 / 15 us, with all of them 194 / 46 / 34; 8e6 14 / 14 / 19 and 194 / 52 / 43;
+    // 1.6e7 16 / 16 / 32 and 210 / 89 / 95; 2.4e7 20 / 22 / 44 and 236 / 130 / 137.
+    auto emit = [&](auto kernel, uint64_t words) {
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)((n_words + words - 1) / words)), dim3(256), 0, s,
                            bits, n_words, n_pairs, block_sums, cand_off, n_reads, cand_bin, cap,
                            surv_pair, surv_read, surv_bin);
+    };
+    if (nb < 128)
+        emit(compact_emit_kernel<kEmitSmall>, kEmitSmall);
+    else if (nb < 512)
+        emit(compact_emit_kernel<kEmitMiddle>, kEmitMiddle);
+    else
+        emit(compact_emit_kernel<kCompactWpb>, kCompactWpb);
     return hipGetLastError();
 }
 
