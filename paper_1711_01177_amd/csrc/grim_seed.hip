@@ -38,31 +38,19 @@ struct SeedBufferCache {
     std::mutex mu;
     std::vector<std::pair<uint8_t *, uint64_t>> bufs;  // (buffer, bytes)
 
-    // a cached buffer of at least `bytes` bytes and at most twice that (plus
-    // 64 MiB), or null
+    // most bytes a list that needs `bytes` holds: a small list does not keep a
+    // large buffer from the lists that need one
+    static uint64_t most(uint64_t bytes) { return 2 * bytes + (64ull << 20); }
+
+    // the smallest cached buffer of at least `bytes` bytes and at most most(bytes),
+    // or null
     uint8_t *take(uint64_t bytes, uint64_t *got)
     {
         std::lock_guard<std::mutex> lk(mu);
         size_t best = bufs.size();
         for (size_t i = 0; i < bufs.size(); ++i)
-            if (bufs[i].second >= bytes && bufs[i].second <= 2 * bytes + (64ull << 20) &&
+            if (bufs[i].second >= bytes && bufs[i].second <= most(bytes) &&
                 (best == bufs.size() || bufs[i].second < bufs[best].second))
-                best = i;
-        if (best == bufs.size())
-            return nullptr;
-        uint8_t *b = bufs[best].first;
-        *got = bufs[best].second;
-        bufs.erase(bufs.begin() + best);
-        return b;
-    }
-    // the largest cached buffer of at least `bytes` bytes, or null
-    uint8_t *take_largest(uint64_t bytes, uint64_t *got)
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        size_t best = bufs.size();
-        for (size_t i = 0; i < bufs.size(); ++i)
-            if (bufs[i].second >= bytes &&
-                (best == bufs.size() || bufs[i].second > bufs[best].second))
                 best = i;
         if (best == bufs.size())
             return nullptr;
@@ -115,6 +103,7 @@ struct grim_seed_index {
     uint64_t tmp_bytes[3] = {0, 0, 0};
     // page-locked words the kernels report a call's hits and pairs in
     uint64_t *h_totals = nullptr;
+    double hits_per_item = -1;   // of the last call with items (below 0: none yet)
     std::shared_ptr<SeedBufferCache> cache;
 };
 
@@ -1047,6 +1036,17 @@ uint8_t *seed_tmp(grim_seed_index *si, int i, uint64_t bytes)
     return si->tmp[i];
 }
 
+// Buffer of a list that needs `need` bytes: a cached one, else a new one (a 32nd
+// more than asked); null when the allocation fails.
+uint8_t *seed_list_buffer(grim_seed_index *si, uint64_t need, uint64_t *got)
+{
+    uint8_t *b = si->cache->take(need, got);
+    if (b)
+        return b;
+    *got = align_up(need + need / 32, 2ull << 20);
+    return hipMalloc(&b, *got) == hipSuccess ? b : nullptr;
+}
+
 }  // namespace
 
 extern "C" int grim_seed_candidates(const grim_seed_index_t *csi, const grim_batch_t *reads,
@@ -1152,15 +1152,22 @@ extern "C" int grim_seed_candidates(const grim_seed_index_t *csi, const grim_bat
     SEED_TRY(hipGetLastError());
     // Every hit's bin, then the per-read lists in place; the result (offsets and
     // bins in one allocation) is no longer than the hits together.  A call that
-    // finds buffers of earlier calls queues all of it for as many hits as those
-    // hold, without waiting for the number (the wait cost 24 us of the chain of 5000
-    // reads, 42 of a million reads); the kernels do nothing when there are more, and
-    // the second round allocates for the number that is known then.
+    // finds buffers of earlier calls for as many hits as the last call's rate gives
+    // its seeds queues all of it without waiting for the number (the wait cost 24 us
+    // of the chain of 5000 reads, 42 of a million reads); the kernels do nothing when
+    // there are more, and the second round allocates for the number that is known
+    // then.  A list whose buffer turns out to be too large for it moves to another.
     {
         const uint64_t offs = align_up((n + 1) * 8, 256);
+        auto list_bytes = [offs](uint64_t hits) { return offs + (hits + 1) * 4; };
         uint64_t hits_cap = 0;
-        if (si->tmp_bytes[2] >= 8)
-            c->buf = si->cache->take_largest(offs + 8, &c->buf_bytes);
+        if (si->hits_per_item >= 0) {
+            // a 64th more than the rate gives; buffers have a 32nd more
+            const uint64_t est =
+                (uint64_t)std::min(si->hits_per_item * (double)n_items * (1 + 1. / 64), 2147483646.);
+            if (si->tmp_bytes[2] >= (est + 1) * 4)
+                c->buf = si->cache->take(list_bytes(est), &c->buf_bytes);
+        }
         if (c->buf) {
             c->cache = si->cache;
             hits_cap = std::min<uint64_t>({si->tmp_bytes[2] / 4 - 1, (c->buf_bytes - offs) / 4 - 1,
@@ -1176,13 +1183,7 @@ extern "C" int grim_seed_candidates(const grim_seed_index_t *csi, const grim_bat
                     goto done;
                 }
                 hits_cap = total_hits;
-                const uint64_t need = offs + (total_hits + 1) * 4;
-                c->buf = si->cache->take(need, &c->buf_bytes);
-                if (!c->buf) {
-                    c->buf_bytes = align_up(need, 2ull << 20);
-                    if (hipMalloc(&c->buf, c->buf_bytes) != hipSuccess)
-                        c->buf = nullptr;
-                }
+                c->buf = seed_list_buffer(si, list_bytes(total_hits), &c->buf_bytes);
                 c->cache = si->cache;
                 if (!c->buf || !seed_tmp(si, 2, (total_hits + 1) * 4)) {
                     rc = GRIM_E_NOMEM;
@@ -1223,11 +1224,29 @@ extern "C" int grim_seed_candidates(const grim_seed_index_t *csi, const grim_bat
             }
             SEED_TRY(hipStreamSynchronize(s));
             n_pairs = si->h_totals[0];
-            if (known || si->h_totals[1] <= hits_cap)
+            total_hits = si->h_totals[1];
+            if (known || total_hits <= hits_cap)
                 break;
             si->cache->give(c->buf, c->buf_bytes);   // too small, and idle: the stream was waited for
             c->buf = nullptr;
             known = true;
+        }
+        if (n_items)
+            si->hits_per_item = (double)total_hits / (double)n_items;
+        uint64_t bytes = 0;
+        uint8_t *fit = nullptr;
+        if (c->buf_bytes > SeedBufferCache::most(list_bytes(total_hits)))
+            fit = seed_list_buffer(si, list_bytes(total_hits), &bytes);
+        if (fit) {
+            hipError_t e = hipMemcpyAsync(fit, c->buf, offs + n_pairs * 4, hipMemcpyDeviceToDevice, s);
+            if (e == hipSuccess)
+                e = hipStreamSynchronize(s);
+            std::swap(c->buf, fit);
+            std::swap(c->buf_bytes, bytes);
+            si->cache->give(fit, bytes);
+            SEED_TRY(e);
+            c->d_off = reinterpret_cast<uint64_t *>(c->buf);
+            c->d_bin = reinterpret_cast<uint32_t *>(c->buf + offs);
         }
     }
     c->n_pairs = n_pairs;
