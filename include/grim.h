@@ -192,8 +192,8 @@ int grim_workspace_size(const grim_index_t *idx, uint64_t n_pairs, const grim_tu
                         uint64_t *bytes);
 
 /* The filter, batched form: one persistent launch over the whole batch.
- * The pair space is cut into tiles (of tile_pairs pairs where the caller or
- * grim_tune chose it, else by the batch's size), a work-list kernel records the
+ * The pair space is cut into tiles (of tile_pairs pairs where the caller chose
+ * it, else by the batch's size), a work-list kernel records the
  * first read of each, and the filter kernel's wavefronts draw tiles from
  * counters.  For each pair it writes counts[k] (int32, the accumulation sum, or
  * -1 for a bin id >= n_bins or an invalid read) and pass bit k (1 iff
@@ -247,8 +247,10 @@ int grim_filter_status(const void *workspace, void *stream, uint32_t *flags);
 
 /* Pick the fastest launch shape for this index and a representative batch by
  * timing each candidate shape on `stream` over the batch's first 2^26 pairs at
- * most (outputs of those pairs are overwritten).  The
- * result is cached per (device, q, max_len) for later calls with tune = NULL. */
+ * most (outputs of those pairs are overwritten).  tile_pairs of the result is 0
+ * where the library's own cut of the pairs is the fastest.  The fastest shape
+ * with that cut is cached per (device, q, max_len) for later calls with tune =
+ * NULL, which cut their pairs by their own number. */
 int grim_tune(const grim_index_t *idx, const grim_batch_t *sample, int32_t *counts,
               uint32_t *pass_bits, void *workspace, uint64_t workspace_bytes, void *stream,
               grim_tuning_t *out);

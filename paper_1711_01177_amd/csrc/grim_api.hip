@@ -84,9 +84,10 @@ const BatchedVariant *find_variant(uint32_t q, uint32_t g, uint32_t u)
 std::mutex g_tune_mu;
 std::map<std::tuple<int, uint32_t, uint32_t>, grim_tuning_t> g_tune_cache;
 
-// The launch shape a call asks for.  *fixed: its tile was chosen (by the caller
-// or by grim_tune), else it is only the default and the library cuts the pairs
-// by their number.
+// The launch shape a call asks for.  *fixed: the caller chose its tile, else that
+// is only what the workspace is checked against and the library cuts the pairs by
+// their number (with grim_tune's shape too: its sample says nothing of the size of
+// later batches).
 int resolve_tuning(const grim_index_t *idx, uint32_t max_len, const grim_tuning_t *tune,
                    grim_tuning_t *out, bool *fixed)
 {
@@ -96,10 +97,8 @@ int resolve_tuning(const grim_index_t *idx, uint32_t max_len, const grim_tuning_
     if (!tune) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find({idx->device, idx->q, max_len});
-        if (it != g_tune_cache.end()) {
+        if (it != g_tune_cache.end())
             t = it->second;
-            *fixed = true;
-        }
     } else {
         if (tune->lanes_per_cand)
             t.lanes_per_cand = tune->lanes_per_cand;
@@ -203,6 +202,27 @@ hipError_t batched_resident(const BatchedVariant *v, int threads, size_t lds, in
     return hipSuccess;
 }
 
+// Wavefronts and LDS of a workgroup of a batched launch, and its workgroups that
+// one CU holds at once.
+struct BatchedShape {
+    int waves, resident;
+    size_t lds;
+};
+
+int batched_shape(const grim_index_t *idx, int npl, const BatchedVariant *v, BatchedShape *out)
+{
+    const size_t per_wave = (size_t)npl * vector_words(idx->q) * 4;
+    if (per_wave > 65536)
+        return GRIM_E_UNSUPPORTED;
+    int waves = 4;
+    while (waves > 1 && per_wave * waves > 65536)
+        --waves;
+    out->waves = waves;
+    out->lds = per_wave * waves;
+    HIP_TRY(batched_resident(v, 64 * waves, out->lds, &out->resident));
+    return GRIM_OK;
+}
+
 // How the pairs of a launch are cut into tickets (FilterArgs).
 struct Tickets {
     uint32_t big_pairs, small_pairs, n_big, n_tickets;
@@ -260,16 +280,13 @@ int enqueue_batched(const grim_index_t *idx, const grim_batch_t *b, int32_t *cou
     const uint64_t n_tiles = div_up(b->n_pairs, t.tile_pairs);
     if (n_tiles >= (1ull << 32) - (1ull << 24))  // the 32-bit ticket counters must not wrap
         return GRIM_E_UNSUPPORTED;
-    const size_t per_wave = (size_t)a.npl * vector_words(idx->q) * 4;
-    int waves = 4;
-    while (waves > 1 && per_wave * waves > 65536)
-        --waves;
-    if (per_wave > 65536)
-        return GRIM_E_UNSUPPORTED;
     const BatchedVariant *v = find_variant(idx->q, t.lanes_per_cand, t.unroll);
-    int resident = 0;
-    HIP_TRY(batched_resident(v, 64 * waves, per_wave * waves, &resident));
-    uint64_t grid = (uint64_t)cu_count(idx->device) * std::min<uint32_t>(t.wg_per_cu, resident);
+    BatchedShape shape;
+    const int rc = batched_shape(idx, a.npl, v, &shape);
+    if (rc)
+        return rc;
+    const int waves = shape.waves;
+    uint64_t grid = (uint64_t)cu_count(idx->device) * std::min<uint32_t>(t.wg_per_cu, shape.resident);
     const uint64_t room = (ws_bytes - kWsHeader) / 4;
     Tickets k = {t.tile_pairs, t.tile_pairs, (uint32_t)n_tiles, (uint32_t)n_tiles};
     if (!fixed)
@@ -289,7 +306,7 @@ int enqueue_batched(const grim_index_t *idx, const grim_batch_t *b, int32_t *cou
     HIP_TRY(launch_worklist(s, a, (uint32_t)(grid * waves)));
     if (k.n_tickets == 0)
         return GRIM_OK;
-    HIP_TRY(launch_filter(v->kernel, dim3((uint32_t)grid), dim3(64 * waves), per_wave * waves, s, a));
+    HIP_TRY(launch_filter(v->kernel, dim3((uint32_t)grid), dim3(64 * waves), shape.lds, s, a));
     return GRIM_OK;
 }
 
@@ -739,31 +756,47 @@ extern "C" int grim_tune(const grim_index_t *idx, const grim_batch_t *sample, in
     sample = &sub;
     int nv = 0;
     const BatchedVariant *vars = batched_variants(&nv);
-    const uint32_t tiles[] = {512, 1024, 2048};
+    // tile 0: the library's own cut of the pairs.  The others are for callers that
+    // pass the result on with batches like the sample; calls with tune = NULL
+    // take the best shape with the library's cut, whatever their size.
+    const uint32_t tiles[] = {0, 512, 1024, 2048};
     const uint32_t occ[] = {4, 8};
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    float best = 1e30f;
-    grim_tuning_t best_t;
+    float best = 1e30f, best_own = 1e30f;
+    grim_tuning_t best_t, own_t;
     grim_default_tuning(idx->q, &best_t);
+    own_t = best_t;
+    const uint32_t default_tile = best_t.tile_pairs;
     for (int i = 0; i < nv; ++i) {
         if ((uint32_t)vars[i].q != idx->q)
             continue;
-        for (uint32_t tp : tiles) {
-            for (uint32_t wg : occ) {
-                grim_tuning_t t = {(uint32_t)vars[i].g, (uint32_t)vars[i].u, tp, wg};
-                if (workspace_bytes < ws_bytes_for(sample->n_pairs, tp))
+        // an unroll above the lanes runs another name's kernel
+        if (std::any_of(vars, vars + i, [&](const BatchedVariant &v) {
+                return v.kernel == vars[i].kernel;
+            }))
+            continue;
+        BatchedShape shape;
+        if (batched_shape(idx, planes_for(idx->q, sample->max_len), &vars[i], &shape))
+            continue;
+        for (uint32_t wg : occ) {
+            if (wg > occ[0] && shape.resident <= (int)occ[0])   // the same grid again
+                continue;
+            for (uint32_t tp : tiles) {
+                grim_tuning_t t = {(uint32_t)vars[i].g, (uint32_t)vars[i].u, tp ? tp : default_tile,
+                                   wg};
+                if (workspace_bytes < ws_bytes_for(sample->n_pairs, t.tile_pairs))
                     continue;
                 if (enqueue_batched(idx, sample, counts, pass_bits, workspace, workspace_bytes, t,
-                                    true, s))
+                                    tp != 0, s))
                     continue;
                 float ms[3];
                 bool fine = true;
                 for (int rep = 0; rep < 3 && fine; ++rep) {
                     fine = hipEventRecord(e0, s) == hipSuccess &&
                            enqueue_batched(idx, sample, counts, pass_bits, workspace,
-                                           workspace_bytes, t, true, s) == GRIM_OK &&
+                                           workspace_bytes, t, tp != 0, s) == GRIM_OK &&
                            hipEventRecord(e1, s) == hipSuccess &&
                            hipEventSynchronize(e1) == hipSuccess &&
                            hipEventElapsedTime(&ms[rep], e0, e1) == hipSuccess;
@@ -774,6 +807,11 @@ extern "C" int grim_tune(const grim_index_t *idx, const grim_batch_t *sample, in
                 if (ms[1] < best) {
                     best = ms[1];
                     best_t = t;
+                    best_t.tile_pairs = tp;
+                }
+                if (!tp && ms[1] < best_own) {
+                    best_own = ms[1];
+                    own_t = t;
                 }
             }
         }
@@ -781,9 +819,12 @@ extern "C" int grim_tune(const grim_index_t *idx, const grim_batch_t *sample, in
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     HIP_TRY(hipStreamSynchronize(s));
+    // a workspace sized for the result is large enough with tune = NULL as well
+    if (best_t.tile_pairs)
+        own_t.tile_pairs = best_t.tile_pairs;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune_cache[{idx->device, idx->q, sample->max_len}] = best_t;
+        g_tune_cache[{idx->device, idx->q, sample->max_len}] = own_t;
     }
     *out = best_t;
     return GRIM_OK;
