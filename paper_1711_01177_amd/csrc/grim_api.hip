@@ -109,6 +109,14 @@ int resolve_tuning(const grim_index_t *idx, uint32_t max_len, const grim_tuning_
         if (tune->wg_per_cu)
             t.wg_per_cu = tune->wg_per_cu;
     }
+    // lanes or an unroll given alone, with a default that no kernel has beside it:
+    // 2 lanes of q = 5 go with an unroll of 4, an unroll of 4 of q = 7 with 64 lanes
+    if (tune && !find_variant(idx->q, t.lanes_per_cand, t.unroll)) {
+        if (idx->q == 5 && !tune->unroll)
+            t.unroll = 4;
+        if (idx->q == 7 && !tune->lanes_per_cand)
+            t.lanes_per_cand = 64;
+    }
     if (t.tile_pairs < 64 || t.tile_pairs > 4096 || t.tile_pairs % 64 != 0)
         return GRIM_E_INVALID;
     if (t.wg_per_cu < 1 || t.wg_per_cu > 32)
