@@ -882,19 +882,19 @@ extern "C" int grim_index_attach_reference(grim_index_t *idx, const uint32_t *re
     if (hipMalloc(&d, (nw + kRefPadWords) * 4) != hipSuccess)
         return GRIM_E_NOMEM;
     if (hipMalloc(&planes, n_planes * 8) != hipSuccess) {
-        (void)hipFree(d);
-        return GRIM_E_NOMEM;
+        planes = nullptr;   // the scan of all columns does without
+        (void)hipGetLastError();
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = hipMemcpyAsync(d, ref_2bit, nw * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = launch_zero(s, d + nw, kRefPadWords);
-    if (e == hipSuccess)
+    if (e == hipSuccess && planes)
         e = launch_zero(s, reinterpret_cast<uint32_t *>(planes), 2 * kPlanePad);
-    if (e == hipSuccess)
+    if (e == hipSuccess && planes)
         e = launch_zero(s, reinterpret_cast<uint32_t *>(planes + n_planes - kPlanePad),
                         2 * kPlanePad);
-    if (e == hipSuccess)
+    if (e == hipSuccess && planes)
         e = launch_planes(s, d, nw, planes + kPlanePad);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
@@ -935,7 +935,7 @@ extern "C" int grim_verify_survivors(const grim_index_t *idx, const grim_batch_t
     std::memset(&a, 0, sizeof(a));
     a.ref = idx->d_ref;
     a.ref_words = idx->ref_words;
-    a.planes = idx->d_planes + kPlanePad;
+    a.planes = idx->d_planes ? idx->d_planes + kPlanePad : nullptr;
     a.G = idx->G;
     a.B = idx->B;
     a.O = idx->O;

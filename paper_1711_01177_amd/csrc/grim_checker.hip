@@ -1175,7 +1175,7 @@ static hipError_t launch_verify_w(hipStream_t s, int cus, const VerifyArgs &a)
     const void *small = reinterpret_cast<const void *>(&verify_kernel<W, kVerifySmall, true>);
     const void *large = reinterpret_cast<const void *>(&verify_kernel<1, kVerifyChunk, false>);
     const uint64_t span = a.B + a.O < a.G ? a.B + a.O : a.G;
-    if (span > (uint64_t)kSpanMax)   // no survivor has pieces
+    if (!a.planes || span > (uint64_t)kSpanMax)   // no survivor has pieces
         return launch_chunks(s, all, resident[0], cus, kVerifySmall, a);
     // chunks of 1024 sort and pack better (2.5M survivors: 512 9 % slower; 5.3e5:
     // 246 us, 256 327 us); lists that would leave CUs without one take chunks of

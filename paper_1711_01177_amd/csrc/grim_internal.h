@@ -64,7 +64,8 @@ constexpr uint64_t kPlanePad = 64;
 struct VerifyArgs {
     const uint32_t *ref;        // packed reference, kRefPadWords zero words after its end
     uint64_t ref_words;
-    const uint2 *planes;        // bit planes of the reference, kPlanePad pairs around them
+    const uint2 *planes;        // bit planes of the reference, kPlanePad pairs around them,
+                                // or null (no room for them)
     uint64_t G, B, O, n_bins;
     const uint32_t *rw;
     uint64_t nw;
@@ -164,7 +165,7 @@ struct grim_index {
     void *d_vec;
     uint32_t *d_ref;        // packed reference kept for alignment checks (or null),
                             // followed by kRefPadWords zero words
-    uint2 *d_planes;        // its bit planes, kPlanePad zero pairs before and after
+    uint2 *d_planes;        // its bit planes, kPlanePad zero pairs before and after (or null)
     uint64_t ref_words;
     uint32_t *d_rows;       // token-major copy for the bin-window form (or null)
     uint64_t row_words;

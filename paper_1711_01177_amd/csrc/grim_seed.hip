@@ -1044,7 +1044,10 @@ uint8_t *seed_list_buffer(grim_seed_index *si, uint64_t need, uint64_t *got)
     if (b)
         return b;
     *got = align_up(need + need / 32, 2ull << 20);
-    return hipMalloc(&b, *got) == hipSuccess ? b : nullptr;
+    if (hipMalloc(&b, *got) == hipSuccess)
+        return b;
+    (void)hipGetLastError();   // a list that only moves stays where it is
+    return nullptr;
 }
 
 }  // namespace
