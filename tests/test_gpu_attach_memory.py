@@ -42,7 +42,16 @@ def test_no_room_for_bit_planes():
         assert np.array_equal(dist.cpu().numpy(), want)
 
     torch.cuda.synchronize()
-    hog = torch.empty(torch.cuda.mem_get_info()[0] - (620 << 20), dtype=torch.uint8, device="cuda")
+    # all memory but 620 MiB: taken until none is left, then given back
+    hog = [torch.empty(torch.cuda.mem_get_info()[0] - (2 << 30), dtype=torch.uint8, device="cuda")]
+    try:
+        while len(hog) < 4000:
+            hog.append(torch.empty(62 << 20, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        pass
+    assert 12 < len(hog) < 4000
+    del hog[-10:]
+    torch.cuda.empty_cache()
     idx.attach_reference(ref)
     del hog
     torch.cuda.empty_cache()
