@@ -835,17 +835,18 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
     constexpr int NW = 2 * W;
     constexpr int kKeys = kPieces + (SCAN ? NW : 0) + 2;   // edits | words | past the chunk's end
     constexpr uint32_t kSettled = ~0u;        // written to memory already
-    constexpr uint32_t kBands = CH + CH / 2, kBroad = 512;
+    constexpr uint32_t kBroad = 512;
     constexpr int U = CH / 256;   // slots per thread
     static_assert(kKeys <= 64, "one wavefront scans the keys");
     __shared__ uint16_t order[CH];
     __shared__ uint32_t cls[64];
     __shared__ uint32_t okw[CH / 32];
     __shared__ uint32_t best[CH];
-    // bands to compute: slot in the low 10 bits, first diagonal + 8192 above
-    __shared__ uint32_t bands[kBands], broad[kBroad];
+    // bands to compute (a survivor has one narrow or wide one, or broad ones): slot in
+    // the low 10 bits, first diagonal + 8192 above
+    __shared__ uint32_t bands[CH], broad[kBroad];
     __shared__ uint16_t rest[CH];             // survivors of phase A for phase C
-    __shared__ uint32_t n_bands, n_narrow, n_wide, n_broad, n_rest;
+    __shared__ uint32_t n_narrow, n_wide, n_broad, n_rest;
     __shared__ uint32_t next_a, next_b;       // wavefront runs of phases A and B handed out
     // phase A: pieces[piece * 256 + thread]; phase C: match masks
     __shared__ uint64_t peq[(SCAN && W > 4 ? 4 * W : 16) * 256];
@@ -878,7 +879,7 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
         if (t < CH / 32)
             okw[t] = 0;
         if (t == 0)
-            n_bands = n_narrow = n_wide = n_broad = n_rest = next_a = next_b = 0;
+            n_narrow = n_wide = n_broad = n_rest = next_a = next_b = 0;
         __syncthreads();
         // class of slot u 256 + t
         int key[U];
@@ -939,12 +940,9 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
             auto entry = [&](int32_t first) { return slot | (uint32_t)(first - E + 8192) << 10; };
             bool done = true;
             if (h1 - h0 < 64 - 2 * E) {
-                done = atomicAdd(&n_bands, 1u) < kBands;
-                if (done) {
-                    const uint32_t at = h1 - h0 < 32 - 2 * E ? atomicAdd(&n_narrow, 1u)
-                                                             : kBands - 1 - atomicAdd(&n_wide, 1u);
-                    bands[at] = entry(h0);
-                }
+                const uint32_t at = h1 - h0 < 32 - 2 * E ? atomicAdd(&n_narrow, 1u)
+                                                         : CH - 1 - atomicAdd(&n_wide, 1u);
+                bands[at] = entry(h0);
             } else {
                 const int32_t step = 128 - 2 * E;
                 for (; done && h0 <= h1; h0 += step) {
@@ -1001,7 +999,7 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
             const int kind = x0 < end4 ? 4 : x0 < end2 ? 2 : 1;
             const uint32_t x = x0 + lane - (kind == 4 ? 0u : kind == 2 ? end4 : end2);
             if (x < (kind == 4 ? n4 : kind == 2 ? n2 : n1)) {
-                const uint32_t e = kind == 4 ? broad[x] : bands[kind == 2 ? kBands - 1 - x : x];
+                const uint32_t e = kind == 4 ? broad[x] : bands[kind == 2 ? CH - 1 - x : x];
                 const uint32_t slot = e & 1023u;
                 const int32_t dlo = (int32_t)(e >> 10) - 8192;
                 const uint32_t v = best[slot];
