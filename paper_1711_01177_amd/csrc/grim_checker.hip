@@ -19,10 +19,10 @@ namespace grim {
 // LDS, in order, and writes them one survivor per thread: every store is
 // coalesced and a thread's bin ids are fetched side by side.  What bounds it is
 // those fetches (at 1.5 % passing, some 1e7 lines of cand_bin, most of 1.5 GB
-// moved).  Measured on 8.3e8 pairs of 4M reads, 12.4M survivors: 21 + 12 + 236 us;
+// moved).  Measured on 8.3e8 pairs of 4M reads, 12.4M survivors: 21 + 11 + 237 us;
 // one thread walking each 128 pairs, its reads searched by two threads a block
 // and 1024 totals scanned at a time, took 40 + 38 + 517.  5.6e5 pairs, 7.4e4
-// survivors: 4 + 2 + 9 us (4 + 5 + 43).
+// survivors: 4 + 3 + 9 us (4 + 5 + 43).
 constexpr int kCompactWpt = 4;                       // bitmask words per thread
 constexpr int kCompactWpb = 256 * kCompactWpt;       // words per block
 
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void compact_count_kernel(const uint32_t *__re
 // One workgroup: in-place exclusive scan of n block totals; *n_out = sum.  Up to
 // 32768 totals at a time go through LDS (one pad word per 32), so that global
 // loads and stores are contiguous while each thread scans consecutive ones: one
-// round of loads and one block scan where 1024 at a time took 25 (38 us; 8 now).
+// round of loads and one block scan where 1024 at a time took 25 (38 us; 11 now).
 constexpr uint32_t kScanRound = 1024 * 32;
 
 __global__ __launch_bounds__(1024) void compact_scan_kernel(uint64_t *sums, uint64_t n, uint64_t *n_out)
@@ -580,7 +580,7 @@ __device__ __forceinline__ int32_t scan_survivor(const VerifyArgs &a, uint64_t i
 //
 // The vector ALUs bound it: 2.5M survivors of 100-250 bases at 5-10 % edits take
 // 3.9e8 wavefront instructions (1.06e9 with the scan of all columns for each)
-// and 0.76 ms (1.64), 0.49 of it phase A; 7.4e4 survivors 0.12 ms (0.41).
+// and 0.76 ms (1.64), 0.49 of it phase A; 7.4e4 survivors 0.14 ms (0.41).
 constexpr int kPieces = 32;          // pieces at most (E <= 31: two bands of E fit 64 diagonals)
 constexpr int kPieceMin = 8;         // bases of a piece at least
 constexpr int kPieceBases = 9;       // bases looked for (8 where a lane's pieces have no more)
@@ -1177,7 +1177,8 @@ static hipError_t launch_verify_w(hipStream_t s, int cus, const VerifyArgs &a)
         return launch_chunks(s, all, resident[0], cus, kVerifySmall, a);
     // chunks of 1024 sort and pack better (2.5M survivors: 512 9 % slower; 5.3e5:
     // 246 us, 256 327 us); lists that would leave CUs without one take chunks of
-    // 256 (7.3e4: 121 us; 64, the wavefronts sharing each survivor's pieces, 144)
+    // 256 (7.4e4: 0.14 ms; 64, the wavefronts sharing each survivor's pieces, took a
+    // fifth longer)
     if (a.n_surv < (uint64_t)(cus > 0 ? cus : 1) * kVerifyChunk)
         return launch_chunks(s, small, resident[1], cus, kVerifySmall, a);
     const hipError_t e = launch_chunks(s, large, resident[2], cus, kVerifyChunk, a);

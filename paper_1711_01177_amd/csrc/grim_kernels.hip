@@ -326,7 +326,7 @@ __device__ __forceinline__ uint64_t div_by(uint64_t x, uint32_t d, double inv)
 //
 // Measured, against the kernel before it (one round trip after another per read,
 // every tile of 1024 pairs drawn from one counter at 11.4 ns a draw): 64 reads x
-// 64 pairs 9.7 us (47.6, of which 4.5 the work list), 100k reads / 2.1e7 pairs on
+// 64 pairs 10.6 us (47.5), of which the work list 1.9 (4.5), 100k reads / 2.1e7 pairs on
 // a 64 MB index 436 us (521; a gather of as many vectors alone takes 372), 8.3e8
 // pairs on the 2 GB index 20.0 ms (20.5; gather alone 19.9), q = 6, 2.0e8 pairs
 // 16.5 ms (17.2), q = 7, 5.1e6 pairs of reads up to 2000 bases 1.40 ms (2.66).
