@@ -238,6 +238,23 @@ struct Tickets {
 
 uint64_t div_up(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
+// Fewest pairs of a ticket with wide vectors, 64 to 512: those whose vectors cost four
+// times the planes of a read of max_len bases (which take as long as max_len / 48
+// vectors of 512 bytes), but no more than a read or a wave has.  q = 6, 5000 reads
+// of 8000 bases, 1-512 candidates each: 432 us, 503 with 64-pair tickets at the end
+// (one tile of 1024 pairs after another, planes from one token a lane at a time: 464);
+// 2000 bases 169, 173 (196).  Reads of up to 1500 bases, 6000 with q = 7, keep 64.
+uint32_t build_pairs(const grim_batch_t *b, uint64_t n_waves, uint64_t vector_bytes)
+{
+    const uint64_t want = std::min({(uint64_t)b->max_len * 512 / vector_bytes / 12,
+                                    b->n_pairs / std::max<uint64_t>(1, b->n_reads),
+                                    b->n_pairs / n_waves});
+    uint32_t p = 64;
+    while (p < 512 && 2 * p <= want)
+        p *= 2;
+    return p;
+}
+
 // Tickets of a launch that leaves the cut to the library, n_waves waves and
 // room for a table of `room` first reads.  A ticket costs its wave a first round
 // trip (reads, ids, vectors), the planes of one more read and a draw from a
@@ -248,20 +265,24 @@ uint64_t div_up(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 // 6.3e6 pairs: 512 135 us, 256 169 us, bound by the draws).  Vectors of 512
 // bytes and more pay for smaller ones: four tickets a wave at any size, and a
 // tail of 64-pair tickets (one large one's pairs per wave) so that the waves end
-// together.  512-pair tickets are also what the workspace's table is sized for;
-// with the tail it holds 1024-pair ones, and finer cuts than that search.
-Tickets auto_tickets(uint64_t n_pairs, uint64_t n_waves, uint64_t vector_bytes, uint64_t room)
+// together.  Where a read's candidates are cut that finely its planes are built
+// once more for every ticket, which for long reads takes as long as the vectors of
+// many pairs: `floor` pairs are the fewest then (build_pairs below).  512-pair
+// tickets are also what the workspace's table is sized for; with the tail it holds
+// 1024-pair ones, and finer cuts than that search.
+Tickets auto_tickets(uint64_t n_pairs, uint64_t n_waves, uint64_t vector_bytes, uint32_t floor,
+                     uint64_t room)
 {
     const bool wide = vector_bytes >= 512;
     auto cut = [&](uint32_t big) {
-        Tickets t = {big, wide ? 64u : big, 0, 0};
+        Tickets t = {big, wide ? floor : big, 0, 0};
         const uint64_t tail = n_waves * big;
         t.n_big = (uint32_t)(n_pairs > tail ? (n_pairs - tail) / big : 0);
         t.n_tickets = t.n_big + (uint32_t)div_up(n_pairs - (uint64_t)t.n_big * big, t.small_pairs);
         return t;
     };
     uint32_t big = 512;
-    while (big > 64 && n_pairs * 2 < n_waves * big * (wide ? 8 : 1))
+    while (big > (wide ? floor : 64u) && n_pairs * 2 < n_waves * big * (wide ? 8 : 1))
         big /= 2;
     const Tickets t = cut(big);
     if (t.n_tickets <= room || !wide || big < 512)
@@ -298,7 +319,8 @@ int enqueue_batched(const grim_index_t *idx, const grim_batch_t *b, int32_t *cou
     const uint64_t room = (ws_bytes - kWsHeader) / 4;
     Tickets k = {t.tile_pairs, t.tile_pairs, (uint32_t)n_tiles, (uint32_t)n_tiles};
     if (!fixed)
-        k = auto_tickets(b->n_pairs, grid * waves, idx->vector_bytes, room);
+        k = auto_tickets(b->n_pairs, grid * waves, idx->vector_bytes,
+                         build_pairs(b, grid * waves, idx->vector_bytes), room);
     a.big_pairs = k.big_pairs;
     a.small_pairs = k.small_pairs;
     a.n_big = k.n_big;

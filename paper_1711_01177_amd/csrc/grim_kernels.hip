@@ -242,14 +242,13 @@ __device__ __forceinline__ uint32_t group_id(uint32_t ids, int first, int u)
     return __shfl(ids, first + u);
 }
 
-// Bit planes of one read's tokens (as build_planes), from the wave's registers:
-// lane l holds packed word l from the read's first one on, the read starting at
-// base po of lane 0's word and ending inside lane 63's.  Four tokens per lane
+// Adds ntok tokens of a read to its bit planes (as add_planes), from the wave's
+// registers: lane l holds packed word l from the first one on, the tokens starting
+// at base po of lane 0's word and ending inside lane 63's.  Four tokens per lane
 // are in flight, and a carry level runs only when some lane needs it, so the
-// number of planes in use comes out uniform without a reduction.  The planes
-// are zero on entry.
+// number of planes reached comes out uniform without a reduction.
 template <int Q>
-__device__ __forceinline__ int build_planes_lanes(uint32_t *planes, int npl, uint32_t word,
+__device__ __forceinline__ int add_planes_lanes(uint32_t *planes, int npl, uint32_t word,
                                                   uint32_t po, uint32_t ntok, int lane)
 {
     constexpr int VW = (1 << (2 * Q)) >> 5;
@@ -487,14 +486,28 @@ __global__ __launch_bounds__(256, batched_waves((1 << (2 * Q)) / 128 / G, U)) vo
             if (po + ntok + Q <= 16u * kWave) {
                 if (j_words != j)
                     words = load_words(j);
-                np = build_planes_lanes<Q>(planes, npl, words, po, ntok, lane);
-                wave_fence();
+                np = add_planes_lanes<Q>(planes, npl, words, po, ntok, lane);
             } else {
-                const uint64_t off =
-                    (uint64_t)__builtin_amdgcn_readlane((uint32_t)(m_off >> 32), j) << 32 |
-                    __builtin_amdgcn_readlane((uint32_t)m_off, j);
-                np = add_planes<Q>(planes, npl, a.rw, a.nw, off, ntok, lane);
+                // longer reads in stretches that the lanes hold, the next one's
+                // words ahead (q = 6, reads of 8000 bases with 1-512 candidates: 503
+                // us, 650 with one token a lane at a time from memory)
+                constexpr uint32_t kStretch = 12 * kWave;
+                const uint64_t first = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(m_off >> 32), j)
+                                            << 32 | __builtin_amdgcn_readlane((uint32_t)m_off, j)) >> 4;
+                auto stretch = [&](uint32_t t) -> uint32_t {
+                    const uint64_t w = first + (t >> 4) + lane;
+                    return t < ntok && w < a.nw ? a.rw[w] : 0u;
+                };
+                uint32_t cur = stretch(0);
+                np = 0;
+                for (uint32_t t = 0; t < ntok; t += kStretch) {
+                    const uint32_t nxt = stretch(t + kStretch);
+                    np = max(np, add_planes_lanes<Q>(planes, npl, cur, po, min(ntok - t, kStretch),
+                                                     lane));
+                    cur = nxt;
+                }
             }
+            wave_fence();
             // planes 0 and 1 stay in registers for the whole segment
 #pragma unroll
             for (int c = 0; c < C; ++c) {
