@@ -819,12 +819,13 @@ __device__ __forceinline__ int32_t band_scan(const uint2 *p, int64_t lo, int32_t
 //
 // SCAN: phase C is the end of the same kernel (short lists, where a second launch
 // costs more than it saves).  Else it is verify_scan_kernel's, for the survivors
-// marked with kScanMark in place of a distance: beside phase A's registers and
-// LDS the scan has 3 wavefronts a SIMD, by itself 8 (4 and 2 for reads of over
-// 128 and 256 bases), and idle ones in chunks of which only a part comes to it
-// (2.5e6 survivors of 100 bases at 15 % edits 1.28 ms, 1.48 in one kernel, 1.33 with
-// the scan alone for every survivor; of 64-250 bases at 8 and 15 % 1.90, 2.30 and
-// 1.99).
+// marked with kScanMark in place of a distance: beside phase A's registers and LDS
+// the scan has 3 wavefronts a SIMD, by itself 8 (4 and 2 for reads of over 128 and
+// 256 bases), and idle ones in chunks of which only a part comes to it (2.5e6
+// survivors of 100 bases at 15 % edits 1.26 ms, 1.47 in one kernel, 1.32 with the scan
+// alone for every survivor; of 64-250 bases at 8 and 15 % 1.89, 2.29 and 1.99).  A few
+// survivors alone take it 110 us, so the list of broad bands has room for those of
+// repeats too (2.8e5 survivors of 250 bases, seeds in repeats: 424 us, 533 with 512).
 constexpr int kVerifyChunk = 1024;
 constexpr int kVerifySmall = 256;
 constexpr int32_t kScanMark = INT32_MIN;
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(256, W > 4 ? 2 : 3) void verify_kernel(VerifyArgs a
     constexpr int NW = 2 * W;
     constexpr int kKeys = kPieces + (SCAN ? NW : 0) + 2;   // edits | words | past the chunk's end
     constexpr uint32_t kSettled = ~0u;        // written to memory already
-    constexpr uint32_t kBroad = 512;
+    constexpr uint32_t kBroad = SCAN ? 512 : CH + CH / 2;   // as many as LDS has room for
     constexpr int U = CH / 256;   // slots per thread
     static_assert(kKeys <= 64, "one wavefront scans the keys");
     __shared__ uint16_t order[CH];
