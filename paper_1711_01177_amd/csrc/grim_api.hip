@@ -267,7 +267,7 @@ uint32_t build_pairs(const grim_batch_t *b, uint64_t n_waves, uint64_t vector_by
 // tail of 64-pair tickets (one large one's pairs per wave) so that the waves end
 // together.  Where a read's candidates are cut that finely its planes are built
 // once more for every ticket, which for long reads takes as long as the vectors of
-// many pairs: `floor` pairs are the fewest then (build_pairs below).  512-pair
+// many pairs: `floor` pairs are the fewest then (build_pairs).  512-pair
 // tickets are also what the workspace's table is sized for; with the tail it holds
 // 1024-pair ones, and finer cuts than that search.
 Tickets auto_tickets(uint64_t n_pairs, uint64_t n_waves, uint64_t vector_bytes, uint32_t floor,
